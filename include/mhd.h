@@ -207,9 +207,10 @@ int mhd_step_batch(mhd_ctx* const* ctxs, const int* nsteps, int n, void* stream)
  * only how the work is split: FP64 results are bit-identical for every shape.
  * mhd_set_launch synchronises the context's stream; it must not be called while
  * a captured graph that contains this context is still to be replayed (the
- * graph keeps the launch grid it was captured with).  mhd_get_launch returns
- * the tile and the z-planes per work-group in effect (either pointer may be
- * NULL). */
+ * graph keeps the launch grid it was captured with).  An automatic length is
+ * chosen for each launch from everything that it covers: mhd_get_launch returns
+ * the tile and the z-planes per work-group in effect when the context is stepped
+ * alone (either pointer may be NULL). */
 int mhd_set_launch(mhd_ctx* ctx, int tile, int zchunk);
 int mhd_get_launch(const mhd_ctx* ctx, int* tile, int* zchunk);
 
@@ -228,7 +229,8 @@ typedef struct {
  * (tile, min(cap, nz)); then refine per shape class: the contexts sharing nz,
  * class by class (most cells first), try every other cap with the rest fixed
  * and keep one that makes the group's launch more than 1 % faster.  Every
- * context is left in its chosen shape (mhd_get_launch reads it; out->zchunk_cap
+ * context is left in its chosen shape (mhd_get_launch reads it; for a group whose
+ * best cap is automatic that is the length it was timed with; out->zchunk_cap
  * is the common cap, out->best_ms the final time).  The first-stage launch reads the current state
  * and writes only the second buffer and the CFL maximum of the cycle being
  * prepared, so the state, t and the next step are unchanged.  Contexts must

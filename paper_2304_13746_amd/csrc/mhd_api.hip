@@ -31,9 +31,9 @@ struct mhd_ctx {
   BoxDesc* desc;     // device copy of this box's descriptor
   double* diag_part; // per-block diagnostic partials
   int tile, zchunk;  // launch shape as requested (zchunk 0 = automatic)
-  int lz;            // z-planes per work-group in effect
+  int lz;            // z-planes per work-group: as requested, or when stepped alone
+  int cols;          // x-y tiles of the box
   int diag_blocks;
-  int tiles;         // stage-kernel blocks for this box
   int stages_valid;  // intermediate buffers hold the last cycle's stage results
 };
 
@@ -313,11 +313,83 @@ struct Roles {
   unsigned char src, dst, base;
 };
 
+// ---- planes per block (lz) of the contexts whose z-chunk is automatic.
+//
+// A block marches lz planes in the time of lz + kHead (the planes at its two ends that
+// its neighbours also compute, and the prologue: 2.1 in FP64 and 2.2 in FP32, from 16^3
+// boxes with 1 to 16 planes per block, 9.4 and 4.9 us a plane).  j blocks that share a
+// CU take 1 + share (j - 1) times as long a plane as one block alone, since one block's
+// waves leave the SIMDs idle while they wait; at most resident_blocks run at once.  N
+// blocks put ceil(N / 256) on a CU, so a launch takes
+//   (lz + kHead) (full rounds of resident blocks + the last, partly filled round),
+// and the rule takes the lz with the smallest, a box of its own with a preference for
+// chunk counts that the XCDs divide.  Measured per RK2 cycle (FP64, in us): 32^3 353
+// with 16 planes, the floor that an earlier rule had, and 68 with 1; 101x75x52 365 with
+// 16 and 242 with 6; 256^3 5.62, 5.64, 5.79, 5.62, 5.46, 5.64, 5.91 and 5.83 ms with 16,
+// 20, 22, 26, 32, 37, 43 and 64, and the rule takes 32.  On five boxes between 128^3 and
+// 256^3 in both precisions its choice is within 3.5 % of the best of ten lengths.
+constexpr int kCus = 256;
+constexpr double kHead = 2.2;
+constexpr double kSlabs = 1.06;
+
+// blocks of these kernels that a CU holds at once (their registers and LDS)
+int resident_blocks(const mhd_params* p) {
+  const bool hydro = p->riemann == MHD_HLLC, f32 = p->precision == MHD_FP32;
+  if (p->recon == MHD_PPM && !f32) return hydro ? 2 : 1;
+  return (f32 ? 3 : 2) + (hydro ? 1 : 0);
+}
+
+long long columns(const mhd_params* p, int tile) {
+  int tx, ty;
+  tile_dims(tile, &tx, &ty);
+  return (long long)((p->nx + tx - 1) / tx) * ((p->ny + ty - 1) / ty);
+}
+
+int chunks(int nz, int lz) { return (nz + lz - 1) / lz; }
+
+double launch_cost(const mhd_params* p, long long blocks, int lz) {
+  const int r = resident_blocks(p);
+  const double share = p->precision == MHD_FP32 ? 0.42 : 0.55;
+  const long long k = (blocks + kCus - 1) / kCus;
+  const long long full = k / r;
+  const int rest = (int)(k % r);
+  return (lz + kHead) * (full * (1.0 + share * (r - 1)) + (rest ? 1.0 + share * (rest - 1) : 0.0));
+}
+
+// The lz of n contexts launched together (n <= kMaxBatch): the requested one, or one
+// common length for all the automatic ones.
+void plan_lz(mhd_ctx* const* c, int n, short* lz) {
+  int zmax = 0;
+  for (int i = 0; i < n; ++i) {
+    lz[i] = (short)c[i]->lz;
+    if (c[i]->zchunk == 0 && c[i]->p.nz > zmax) zmax = c[i]->p.nz;
+  }
+  if (zmax == 0) return;
+  double best = 0.0;
+  int pick = 0;
+  // every length for one box (planned once, when it takes its launch shape); for a
+  // group, planned as boxes leave it, every length up to 16 and then steps of an eighth
+  for (int z = 1; z <= zmax; z += n == 1 || z < 16 ? 1 : z / 8) {
+    long long blocks = 0;
+    for (int i = 0; i < n; ++i)
+      blocks += (long long)c[i]->cols * chunks(c[i]->p.nz, c[i]->zchunk ? c[i]->lz : z);
+    double t = launch_cost(&c[0]->p, blocks, z);
+    // a large box: whole z-slabs for each of the 8 XCDs, or halo planes miss its L2
+    if (n == 1 && blocks >= 4 * kCus && chunks(zmax, z) % 8 != 0) t *= kSlabs;
+    if (pick == 0 || t < best) {
+      best = t;
+      pick = z;
+    }
+  }
+  for (int i = 0; i < n; ++i)
+    if (c[i]->zchunk == 0) lz[i] = (short)(pick < c[i]->p.nz ? pick : c[i]->p.nz);
+}
+
 // One stage launch over n contexts sharing precision, solver and tile, with
-// weights (w, w0) for a combining stage.  Batches beyond kMaxBatch go out in
-// chunks.
+// weights (w, w0) for a combining stage and lz[i] planes per block of context i
+// (null: planned here).  Batches beyond kMaxBatch go out in chunks.
 hipError_t launch_stage(mhd_ctx* const* c, const Roles* r, int n, int mode, double w, double w0,
-                        hipStream_t st) {
+                        const short* lz, hipStream_t st) {
   for (int i0 = 0; i0 < n; i0 += kMaxBatch) {
     const int m = n - i0 < kMaxBatch ? n - i0 : kMaxBatch;
     BatchArgs ba = {};
@@ -327,14 +399,19 @@ hipError_t launch_stage(mhd_ctx* const* c, const Roles* r, int n, int mode, doub
     ba.w0 = w0;
     ba.emf = c[i0]->p.emf;
     ba.ct = c[i0]->p.ct;
+    if (lz)
+      memcpy(ba.lz, lz + i0, sizeof(short) * m);
+    else
+      plan_lz(c + i0, m, ba.lz);
     int g = 0;
     for (int i = 0; i < m; ++i) {
-      ba.desc[i] = c[i0 + i]->desc;
+      const mhd_ctx* ci = c[i0 + i];
+      ba.desc[i] = ci->desc;
       ba.start[i] = g;
       ba.src[i] = r[i0 + i].src;
       ba.dst[i] = r[i0 + i].dst;
       ba.base[i] = r[i0 + i].base;
-      g += c[i0 + i]->tiles;
+      g += (int)ci->cols * chunks(ci->p.nz, ba.lz[i]);
     }
     ba.start[m] = g;
     ba.total = g;
@@ -437,6 +514,7 @@ int step_group(mhd_ctx* const* c, const int* nsteps, int n, const double* t_stop
   static thread_local mhd_ctx* act[4096];
   static thread_local Roles roles[4096];
   static thread_local double ts[4096];
+  static thread_local short lz[4096];
   int m = 0;
   for (int i = 0; i < n; ++i)
     if (nsteps[i] > 0) { act[m] = c[i]; ts[m] = t_stop ? t_stop[i] : 0.0; ++m; }
@@ -446,9 +524,12 @@ int step_group(mhd_ctx* const* c, const int* nsteps, int n, const double* t_stop
   const bool uct = c[0]->p.emf == MHD_EMF_UCT_HLL || c[0]->p.emf == MHD_EMF_UCT_HLLD;
   for (int cyc = 0; cyc < maxs; ++cyc) {
     Range cycle("mhd cycle");
+    const int was = m;
     m = 0;
     for (int i = 0; i < n; ++i)
       if (nsteps[i] > cyc) { act[m] = c[i]; ts[m] = t_stop ? t_stop[i] : 0.0; ++m; }
+    if (cyc == 0 || m != was)  // boxes only ever leave
+      for (int i = 0; i < m; i += kMaxBatch) plan_lz(act + i, m - i < kMaxBatch ? m - i : kMaxBatch, lz + i);
     // stage 1: U_1 = S_dt(U_0), measuring the next dt (eq. cfl)
     for (int i = 0; i < m; ++i) {
       const int u0 = act[i]->cur;
@@ -458,7 +539,7 @@ int step_group(mhd_ctx* const* c, const int* nsteps, int n, const double* t_stop
     // and the curl, with UCT-HLL by the edge solve and the face-field update
     // (same roles and weights)
     auto stage = [&](int mode, double w, double w0) -> bool {
-      if (launch_stage(act, roles, m, mode, w, w0, st) != hipSuccess) return false;
+      if (launch_stage(act, roles, m, mode, w, w0, lz, st) != hipSuccess) return false;
       if (uct && launch_uct(act, roles, m, mode, w, w0, !vp, st) != hipSuccess) return false;
       return !vp || launch_vpot(act, roles, m, mode, w, w0, true, st) == hipSuccess;
     };
@@ -483,23 +564,6 @@ int step_group(mhd_ctx* const* c, const int* nsteps, int n, const double* t_stop
   return MHD_OK;
 }
 
-int choose_lz(int tile, int nx, int ny, int nz) {
-  int tx, ty;
-  tile_dims(tile, &tx, &ty);
-  long long tiles = (long long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty);
-  // aim for >= 2048 blocks (8 per CU) with a number of z-chunks that is a
-  // multiple of the 8 XCDs, so that the XCD-aware block order gives each XCD
-  // whole z-slabs (measured at 256^3: 7% (FP64) and 3% (FP32) faster than 6
-  // chunks; at 512^3 FP32 up to 13%); chunks of at least 16 planes
-  long long want = (2048 + tiles - 1) / tiles;
-  want = (want + 7) / 8 * 8;
-  int lz = (int)((nz + want - 1) / want);
-  if (lz < 16) lz = 16;
-  if (lz > nz) lz = nz;
-  return lz;
-}
-
-
 // Give c the launch shape (tile, zchunk; 0 = automatic): raise the dynamic-LDS
 // limit of the tile's kernels and rewrite the box descriptor on the device.
 // Synchronous: kernels in flight on c's stream may still read the old one.
@@ -512,7 +576,6 @@ int apply_shape(mhd_ctx* c, int tile, int zchunk) {
   none.ct = p->ct;
   hipError_t e = stage_kernel(p, none, tile, nullptr, true);
   if (e != hipSuccess) return MHD_ERR_HIP;
-  const int lz = zchunk > 0 ? (zchunk < p->nz ? zchunk : p->nz) : choose_lz(tile, p->nx, p->ny, p->nz);
   BoxDesc d = {};
   for (int b = 0; b < c->nbuf; ++b)
     for (int f = 0; f < c->nfield; ++f) d.buf[b][f] = c->buf[b][f];
@@ -525,8 +588,6 @@ int apply_shape(mhd_ctx* c, int tile, int zchunk) {
   d.nz = p->nz;
   d.ntx = (p->nx + tx - 1) / tx;
   d.nty = (p->ny + ty - 1) / ty;
-  d.lz = lz;
-  d.nzc = (p->nz + lz - 1) / lz;
   for (int k = 0; k < 3; ++k) d.idl[k] = c->idl[k];
   d.gamma = p->gamma;
   d.sc = c->sc;
@@ -537,8 +598,13 @@ int apply_shape(mhd_ctx* c, int tile, int zchunk) {
     return MHD_ERR_HIP;
   c->tile = tile;
   c->zchunk = zchunk;
-  c->lz = lz;
-  c->tiles = d.ntx * d.nty * d.nzc;
+  c->cols = (int)columns(p, tile);
+  c->lz = zchunk < p->nz ? zchunk : p->nz;
+  if (zchunk == 0) {
+    short lz;
+    plan_lz(&c, 1, &lz);
+    c->lz = lz;
+  }
   return MHD_OK;
 }
 
@@ -563,11 +629,6 @@ int tile_dims(int tile, int* tx, int* ty) {
   if (tile == TILE_24x8) { *tx = 24; *ty = 8; return 1; }
   if (tile == TILE_18x11) { *tx = 18; *ty = 11; return 1; }
   return 0;
-}
-int stage_blocks(int tile, int nx, int ny, int nz, int lz) {
-  int tx, ty;
-  if (!tile_dims(tile, &tx, &ty)) return 0;
-  return ((nx + tx - 1) / tx) * ((ny + ty - 1) / ty) * ((nz + lz - 1) / lz);
 }
 }  // namespace mhd
 
@@ -688,7 +749,7 @@ int mhd_set_state(mhd_ctx* c, const mhd_state_view* v, double t, double dt_next)
   if (!(dt_next > 0.0)) {
     // eq. (cfl) on the initial state: the stage kernel in measuring mode
     const Roles r0 = {0, 1, 0};
-    if (launch_stage(&c, &r0, 1, 2, 1.0, 0.0, c->stream) != hipSuccess) return MHD_ERR_HIP;
+    if (launch_stage(&c, &r0, 1, 2, 1.0, 0.0, nullptr, c->stream) != hipSuccess) return MHD_ERR_HIP;
     hipLaunchKernelGGL(k_init_dt, dim3(1), dim3(1), 0, c->stream, c->sc);
     if (hipGetLastError() != hipSuccess) return MHD_ERR_HIP;
   }
@@ -814,7 +875,7 @@ int mhd_tune(mhd_ctx* const* ctxs, int n, int reps, void* stream, mhd_tune_resul
   // first launch warms up)
   auto time_group = [&](float* med) -> int {
     for (int r = 0; r <= reps; ++r) {
-      if (hipEventRecord(e0, st) != hipSuccess || launch_stage(ctxs, src, n, 0, 1.0, 0.0, st) != hipSuccess ||
+      if (hipEventRecord(e0, st) != hipSuccess || launch_stage(ctxs, src, n, 0, 1.0, 0.0, nullptr, st) != hipSuccess ||
           hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess)
         return MHD_ERR_HIP;
       float ms = 0.0f;
@@ -923,6 +984,17 @@ int mhd_tune(mhd_ctx* const* ctxs, int n, int reps, void* stream, mhd_tune_resul
   for (int i = 0; i < n; ++i) ctxs[i]->stages_valid = 0;
   if (rc == MHD_OK)
     for (int i = 0; i < n && rc == MHD_OK; ++i) rc = apply_shape(ctxs[i], best_tile, cls_cap[i]);
+  // an automatic length depends on what is launched together: a group's is fixed as
+  // it was timed, so that mhd_get_launch reports it
+  if (rc == MHD_OK && n > 1) {
+    for (int i0 = 0; i0 < n; i0 += kMaxBatch) {
+      const int m = n - i0 < kMaxBatch ? n - i0 : kMaxBatch;
+      short lz[kMaxBatch];
+      plan_lz(ctxs + i0, m, lz);
+      for (int i = 0; i < m && rc == MHD_OK; ++i)
+        if (cls_cap[i0 + i] == 0) rc = apply_shape(ctxs[i0 + i], best_tile, lz[i]);
+    }
+  }
   free(cls_cap);
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);

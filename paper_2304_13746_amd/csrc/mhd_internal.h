@@ -52,7 +52,8 @@ __device__ __forceinline__ void st_agent(unsigned* p, unsigned v) {
 enum { TILE_16x16 = 1, TILE_24x8 = 2, TILE_18x11 = 3 };
 
 // One box as the stage kernel sees it; each context keeps its descriptor in its
-// own workspace (rewritten only when its launch shape changes).
+// own workspace (rewritten only when its launch shape changes).  How many z-planes a
+// block marches is a property of the launch, not of the box: see BatchArgs::lz.
 constexpr int kMaxBuf = 3;  // state buffers: U_0 and up to two stage results
 // fields of a buffer: rho mx my mz en bx by bz, and with the vector-potential
 // form of constrained transport the edge potential ax ay az
@@ -61,7 +62,7 @@ enum { CT_FACE = 0, CT_VECPOT = 1 };
 struct BoxDesc {
   void* buf[kMaxBuf][kFields];
   int nx, ny, nz;
-  int ntx, nty, nzc, lz;  // tiles of the context's tile shape, z-chunks
+  int ntx, nty;           // tiles of the context's tile shape
   int ct;                 // CT_FACE or CT_VECPOT
   double idl[3];          // 1 / dl_d
   double gamma;
@@ -89,6 +90,7 @@ struct BatchArgs {
   double w, w0;
   const BoxDesc* desc[kMaxBatch];
   int start[kMaxBatch + 1];
+  short lz[kMaxBatch];  // stage launch: z-planes per block of each box
   unsigned char src[kMaxBatch], dst[kMaxBatch], base[kMaxBatch];
 };
 
