@@ -85,13 +85,124 @@ __device__ double clip_step(double dt, double t, double t_stop) {
   return dt;
 }
 
-__global__ void k_set(Scalars* s, double t, double dt_next, double cfl) {
+__device__ void set_scalars(Scalars* s, double t, double dt_next, double cfl) {
   st_agent(&s->t, t);
   st_agent(&s->dt_next, dt_next);
   st_agent(&s->dt, 0.0);
   st_agent(&s->cfl, cfl);
   st_agent(&s->invdt_bits, 0ull);
   st_agent(&s->status, 0u);
+}
+
+__global__ void k_set(Scalars* s, double t, double dt_next, double cfl) {
+  set_scalars(s, t, dt_next, cfl);
+}
+
+// ---- state copies: all fields of a state in one launch, with the scalars of a new
+// state.  For small boxes a copy is all launch: eight copies cost 8 to 10 us each on
+// the host and left the GPU idle between them, one pass of set_state, a cycle and
+// get_state on a 16^3 box 193 us; one launch each way takes it to 145 us.  Large ones
+// run at the card's copy rate either way.
+constexpr int kCopyThreads = 256;
+struct CopyArgs {
+  const void* src[kFields];
+  void* dst[kFields];
+  long long bytes;  // of one field, a multiple of 4
+  Scalars* sc;      // null: leave the scalars alone
+  double t, dt_next, cfl;
+};
+
+typedef unsigned Words4 __attribute__((ext_vector_type(4)));
+typedef unsigned Words2 __attribute__((ext_vector_type(2)));
+
+template <typename V>
+__device__ __forceinline__ void copy_field(const void* src, void* dst, long long bytes) {
+  const V* s = static_cast<const V*>(src);
+  V* d = static_cast<V*>(dst);
+  const long long n = bytes / (long long)sizeof(V), step = (long long)gridDim.x * kCopyThreads;
+  long long c = (long long)blockIdx.x * kCopyThreads + threadIdx.x;
+  for (; c + 3 * step < n; c += 4 * step) {
+    const V v0 = s[c], v1 = s[c + step], v2 = s[c + 2 * step], v3 = s[c + 3 * step];
+    d[c] = v0;
+    d[c + step] = v1;
+    d[c + 2 * step] = v2;
+    d[c + 3 * step] = v3;
+  }
+  for (; c < n; c += step) d[c] = s[c];
+  // what a vector does not divide
+  const long long w = n * (long long)(sizeof(V) / 4) + threadIdx.x;
+  if (blockIdx.x == 0 && w < bytes / 4)
+    static_cast<unsigned*>(dst)[w] = static_cast<const unsigned*>(src)[w];
+}
+
+__global__ void __launch_bounds__(kCopyThreads) k_copy(CopyArgs a) {
+  if (a.sc && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
+    set_scalars(a.sc, a.t, a.dt_next, a.cfl);
+  const void* src = a.src[blockIdx.y];
+  void* dst = a.dst[blockIdx.y];
+  const unsigned long long low = (uintptr_t)src | (uintptr_t)dst;
+  if ((low & 15) == 0)  // the caller's arrays need not be aligned beyond their values
+    copy_field<Words4>(src, dst, a.bytes);
+  else if ((low & 7) == 0)
+    copy_field<Words2>(src, dst, a.bytes);
+  else
+    copy_field<unsigned>(src, dst, a.bytes);
+}
+
+// Whether a kernel on device dev may touch [p, p + bytes): memory of that device, inside
+// one allocation.  Anything else (another device's memory, host memory, an array that is
+// too short) is left to hipMemcpyAsync and its checks.  The two look-ups take about 3 us
+// on the host; the arrays of a small state mostly lie in one allocation, looked up once.
+struct Extent {
+  uintptr_t lo, hi;
+};
+bool on_device(const void* ptr, size_t bytes, int dev, Extent& known) {
+  const uintptr_t p = (uintptr_t)ptr;
+  if ((p & 3) != 0) return false;
+  if (p >= known.lo && p + bytes <= known.hi) return true;
+  hipPointerAttribute_t at;
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipPointerGetAttributes(&at, ptr) == hipSuccess && at.type == hipMemoryTypeDevice &&
+      at.device == dev && hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)ptr) == hipSuccess) {
+    known = {(uintptr_t)base, (uintptr_t)base + size};
+    return p + bytes <= known.hi;
+  }
+  (void)hipGetLastError();
+  return false;
+}
+
+// Copy nf fields (null sources are skipped) on st; with sc also set the scalars.
+// view: the caller's side of the copy, whose memory is looked at first.
+hipError_t copy_fields(void* const* dst, void* const* src, int nf, size_t bytes, void* const* view,
+                       int dev, Scalars* sc, double t, double dt_next, double cfl, hipStream_t st) {
+  CopyArgs a = {};
+  int n = 0;
+  bool direct = true;
+  Extent known = {0, 0};
+  for (int f = 0; f < nf; ++f) {
+    if (!src[f]) continue;
+    direct = direct && on_device(view[f], bytes, dev, known);
+    a.src[n] = src[f];
+    a.dst[n++] = dst[f];
+  }
+  if (!direct) {
+    for (int f = 0; f < n; ++f) {
+      hipError_t e = hipMemcpyAsync(a.dst[f], a.src[f], bytes, hipMemcpyDeviceToDevice, st);
+      if (e != hipSuccess) return e;
+    }
+    if (sc) hipLaunchKernelGGL(k_set, dim3(1), dim3(1), 0, st, sc, t, dt_next, cfl);
+    return hipGetLastError();
+  }
+  a.bytes = (long long)bytes;
+  a.sc = sc;
+  a.t = t;
+  a.dt_next = dt_next;
+  a.cfl = cfl;
+  // four 16-byte vectors a thread, up to 8 blocks per CU over the fields of a state
+  const size_t want = (bytes + 64 * kCopyThreads - 1) / (64 * kCopyThreads);
+  hipLaunchKernelGGL(k_copy, dim3((unsigned)(want < 256 ? want : 256), n), dim3(kCopyThreads), 0, st, a);
+  return hipGetLastError();
 }
 
 __device__ double invdt_max(Scalars* s) {
@@ -780,17 +891,14 @@ int mhd_set_state(mhd_ctx* c, const mhd_state_view* v, double t, double dt_next)
   const size_t bytes = (size_t)c->ncell * c->elem;
   c->cur = 0;
   c->stages_valid = 0;
-  for (int f = 0; f < c->nfield; ++f) {
-    if (vp && f >= 5 && f < 8) continue;
-    hipError_t e = hipMemcpyAsync(c->buf[0][f], src[f], bytes, hipMemcpyDeviceToDevice, c->stream);
-    if (e != hipSuccess) return MHD_ERR_HIP;
-  }
+  if (vp) src[5] = src[6] = src[7] = nullptr;
+  if (copy_fields(c->buf[0], src, c->nfield, bytes, src, c->device, c->sc, t, dt_next, c->p.cfl,
+                  c->stream) != hipSuccess)
+    return MHD_ERR_HIP;
   if (vp) {
     const Roles r0 = {0, 0, 0};
     if (launch_vpot(&c, &r0, 1, 0, 1.0, 0.0, false, c->stream) != hipSuccess) return MHD_ERR_HIP;
   }
-  hipLaunchKernelGGL(k_set, dim3(1), dim3(1), 0, c->stream, c->sc, t, dt_next, c->p.cfl);
-  if (hipGetLastError() != hipSuccess) return MHD_ERR_HIP;
   if (!(dt_next > 0.0)) {
     // eq. (cfl) on the initial state: the stage kernel in measuring mode
     const Roles r0 = {0, 1, 0};
@@ -817,10 +925,9 @@ int mhd_get_state(mhd_ctx* c, const mhd_state_view* v, double* t, double* dt_nex
       if (!dst[f]) return MHD_ERR_INVALID_ARG;
     // the potential is copied out when the view asks for it
     const int nf = c->nfield == 11 && dst[8] && dst[9] && dst[10] ? 11 : 8;
-    for (int f = 0; f < nf; ++f) {
-      hipError_t e = hipMemcpyAsync(dst[f], c->buf[c->cur][f], bytes, hipMemcpyDeviceToDevice, c->stream);
-      if (e != hipSuccess) return MHD_ERR_HIP;
-    }
+    if (copy_fields(dst, c->buf[c->cur], nf, bytes, dst, c->device, nullptr, 0.0, 0.0, 0.0,
+                    c->stream) != hipSuccess)
+      return MHD_ERR_HIP;
   }
   Scalars h;
   hipError_t e = hipMemcpyAsync(&h, c->sc, sizeof(Scalars), hipMemcpyDeviceToHost, c->stream);
@@ -843,10 +950,9 @@ int mhd_get_stage_output(mhd_ctx* c, int stage, const mhd_state_view* v) {
     if (!dst[f]) return MHD_ERR_INVALID_ARG;
   const int nf = c->nfield == 11 && dst[8] && dst[9] && dst[10] ? 11 : 8;
   const size_t bytes = (size_t)c->ncell * c->elem;
-  for (int f = 0; f < nf; ++f) {
-    hipError_t e = hipMemcpyAsync(dst[f], c->buf[stage][f], bytes, hipMemcpyDeviceToDevice, c->stream);
-    if (e != hipSuccess) return MHD_ERR_HIP;
-  }
+  if (copy_fields(dst, c->buf[stage], nf, bytes, dst, c->device, nullptr, 0.0, 0.0, 0.0, c->stream) !=
+      hipSuccess)
+    return MHD_ERR_HIP;
   return hipStreamSynchronize(c->stream) == hipSuccess ? MHD_OK : MHD_ERR_HIP;
 }
 
