@@ -76,19 +76,11 @@ int nscratch_of(const mhd_params* p) {
 
 // ---- cycle control kernels (one thread): everything stays on the device
 
-__device__ double clip_step(double dt, double t, double t_stop) {
-  if (t_stop > 0.0) {
-    double rem = t_stop - t;
-    if (dt > rem) dt = rem;
-    if (!(dt > 0.0)) dt = 0.0;
-  }
-  return dt;
-}
-
 __device__ void set_scalars(Scalars* s, double t, double dt_next, double cfl) {
   st_agent(&s->t, t);
   st_agent(&s->dt_next, dt_next);
-  st_agent(&s->dt, 0.0);
+  st_agent(&s->dt[0], 0.0);
+  st_agent(&s->dt[1], 0.0);
   st_agent(&s->cfl, cfl);
   st_agent(&s->invdt_bits, 0ull);
   st_agent(&s->status, 0u);
@@ -218,31 +210,21 @@ __global__ void k_init_dt(Scalars* s) {
 // cycle control for up to kMaxBatch boxes, one thread per box
 struct CtlArgs {
   int n;
-  int pad;
+  int par;
   Scalars* sc[kMaxBatch];
   double t_stop[kMaxBatch];
 };
 
-__global__ void k_begin(CtlArgs a) {
+// forget the CFL maximum measured so far (timed first stages)
+__global__ void k_unmeasure(CtlArgs a) {
   const int i = threadIdx.x;
-  if (i >= a.n) return;
-  Scalars* s = a.sc[i];
-  st_agent(&s->dt, clip_step(ld_agent(&s->dt_next), ld_agent(&s->t), a.t_stop[i]));
-  st_agent(&s->invdt_bits, 0ull);
+  if (i < a.n) st_agent(&a.sc[i]->invdt_bits, 0ull);
 }
 
-// end of a cycle: advance t, take the step measured during its first stage,
-// clip the next cycle's step
+// end of an Euler cycle, whose only stage also measures the CFL maximum
 __global__ void k_end(CtlArgs a) {
   const int i = threadIdx.x;
-  if (i >= a.n) return;
-  Scalars* s = a.sc[i];
-  const double t = ld_agent(&s->t) + ld_agent(&s->dt);
-  const double dtn = ld_agent(&s->cfl) / invdt_max(s);
-  st_agent(&s->t, t);
-  st_agent(&s->dt_next, dtn);
-  st_agent(&s->dt, clip_step(dtn, t, a.t_stop[i]));
-  st_agent(&s->invdt_bits, 0ull);
+  if (i < a.n) end_cycle(a.sc[i], a.par, a.t_stop[i]);
 }
 
 // ---- diagnostics: Neumaier-compensated sums in FP64
@@ -542,8 +524,13 @@ void plan_lz(mhd_ctx* const* c, int n, short* lz) {
 // One stage launch over n contexts sharing precision, solver and tile, with
 // weights (w, w0) for a combining stage and lz[i] planes per block of context i
 // (null: planned here).  Batches beyond kMaxBatch go out in chunks.
+struct Control {
+  int par, first, last;   // as in BatchArgs
+  const double* t_stop;   // per context
+};
+
 hipError_t launch_stage(mhd_ctx* const* c, const Roles* r, int n, int mode, double w, double w0,
-                        const short* lz, hipStream_t st) {
+                        const short* lz, const Control& ctl, hipStream_t st) {
   for (int i0 = 0; i0 < n; i0 += kMaxBatch) {
     const int m = n - i0 < kMaxBatch ? n - i0 : kMaxBatch;
     BatchArgs ba = {};
@@ -553,6 +540,10 @@ hipError_t launch_stage(mhd_ctx* const* c, const Roles* r, int n, int mode, doub
     ba.w0 = w0;
     ba.emf = c[i0]->p.emf;
     ba.ct = c[i0]->p.ct;
+    ba.par = ctl.par;
+    ba.first = ctl.first;
+    ba.last = ctl.last;
+    if (ctl.t_stop) memcpy(ba.t_stop, ctl.t_stop + i0, sizeof(double) * m);
     if (lz)
       memcpy(ba.lz, lz + i0, sizeof(short) * m);
     else
@@ -579,7 +570,7 @@ hipError_t launch_stage(mhd_ctx* const* c, const Roles* r, int n, int mode, doub
 // UCT-HLL after a stage launch (mode 0: first stage, 1: combining stage): the
 // edge EMFs from the exported face data, then the face-field update.
 hipError_t launch_uct(mhd_ctx* const* c, const Roles* r, int n, int mode, double w, double w0,
-                      bool update_b, hipStream_t st) {
+                      int par, bool update_b, hipStream_t st) {
   for (int i0 = 0; i0 < n; i0 += kMaxBatch) {
     const int m = n - i0 < kMaxBatch ? n - i0 : kMaxBatch;
     BatchArgs ba = {};
@@ -588,6 +579,7 @@ hipError_t launch_uct(mhd_ctx* const* c, const Roles* r, int n, int mode, double
     ba.w = w;
     ba.w0 = w0;
     ba.emf = c[i0]->p.emf;
+    ba.par = par;
     int g = 0;
     for (int i = 0; i < m; ++i) {
       ba.desc[i] = c[i0 + i]->desc;
@@ -611,7 +603,7 @@ hipError_t launch_uct(mhd_ctx* const* c, const Roles* r, int n, int mode, double
 // stage): A update on every edge, then the face field from curl A; update =
 // false runs only the curl (deriving B from a potential the caller set).
 hipError_t launch_vpot(mhd_ctx* const* c, const Roles* r, int n, int mode, double w, double w0,
-                       bool update, hipStream_t st) {
+                       int par, bool update, hipStream_t st) {
   for (int i0 = 0; i0 < n; i0 += kMaxBatch) {
     const int m = n - i0 < kMaxBatch ? n - i0 : kMaxBatch;
     BatchArgs ba = {};
@@ -620,6 +612,7 @@ hipError_t launch_vpot(mhd_ctx* const* c, const Roles* r, int n, int mode, doubl
     ba.w = w;
     ba.w0 = w0;
     ba.emf = c[i0]->p.emf;
+    ba.par = par;
     int g = 0;
     for (int i = 0; i < m; ++i) {
       ba.desc[i] = c[i0 + i]->desc;
@@ -638,19 +631,18 @@ hipError_t launch_vpot(mhd_ctx* const* c, const Roles* r, int n, int mode, doubl
   return hipSuccess;
 }
 
-hipError_t launch_ctl(bool begin, mhd_ctx* const* c, int n, const double* t_stop, hipStream_t st) {
+hipError_t launch_ctl(void (*kernel)(CtlArgs), mhd_ctx* const* c, int n, int par,
+                      const double* t_stop, hipStream_t st) {
   for (int i0 = 0; i0 < n; i0 += kMaxBatch) {
     const int m = n - i0 < kMaxBatch ? n - i0 : kMaxBatch;
     CtlArgs a = {};
     a.n = m;
+    a.par = par;
     for (int i = 0; i < m; ++i) {
       a.sc[i] = c[i0 + i]->sc;
       a.t_stop[i] = t_stop ? t_stop[i0 + i] : 0.0;
     }
-    if (begin)
-      hipLaunchKernelGGL(k_begin, dim3(1), dim3(kMaxBatch), 0, st, a);
-    else
-      hipLaunchKernelGGL(k_end, dim3(1), dim3(kMaxBatch), 0, st, a);
+    hipLaunchKernelGGL(kernel, dim3(1), dim3(kMaxBatch), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -670,9 +662,6 @@ int step_group(mhd_ctx* const* c, const int* nsteps, int n, const double* t_stop
   static thread_local double ts[4096];
   static thread_local short lz[4096];
   int m = 0;
-  for (int i = 0; i < n; ++i)
-    if (nsteps[i] > 0) { act[m] = c[i]; ts[m] = t_stop ? t_stop[i] : 0.0; ++m; }
-  if (launch_ctl(true, act, m, ts, st) != hipSuccess) return MHD_ERR_HIP;
   const int integ = c[0]->p.integrator;
   const bool vp = c[0]->p.ct == MHD_CT_VECPOT;
   const bool uct = c[0]->p.emf == MHD_EMF_UCT_HLL || c[0]->p.emf == MHD_EMF_UCT_HLLD;
@@ -692,27 +681,29 @@ int step_group(mhd_ctx* const* c, const int* nsteps, int n, const double* t_stop
     // with the vector-potential form every stage is followed by the A update
     // and the curl, with UCT-HLL by the edge solve and the face-field update
     // (same roles and weights)
-    auto stage = [&](int mode, double w, double w0) -> bool {
-      if (launch_stage(act, roles, m, mode, w, w0, lz, st) != hipSuccess) return false;
-      if (uct && launch_uct(act, roles, m, mode, w, w0, !vp, st) != hipSuccess) return false;
-      return !vp || launch_vpot(act, roles, m, mode, w, w0, true, st) == hipSuccess;
+    const int par = cyc & 1;
+    auto stage = [&](int mode, double w, double w0, bool last) -> bool {
+      const Control ctl = {par, cyc == 0 && mode == 0, last, ts};
+      if (launch_stage(act, roles, m, mode, w, w0, lz, ctl, st) != hipSuccess) return false;
+      if (uct && launch_uct(act, roles, m, mode, w, w0, par, !vp, st) != hipSuccess) return false;
+      return !vp || launch_vpot(act, roles, m, mode, w, w0, par, true, st) == hipSuccess;
     };
-    if (!stage(0, 1.0, 0.0)) return MHD_ERR_HIP;
+    if (!stage(0, 1.0, 0.0, false)) return MHD_ERR_HIP;
     if (integ == MHD_RK2) {
       // U^{n+1} = 1/2 S_dt(U_1) + 1/2 U_0, written over U_0
       for (int i = 0; i < m; ++i) roles[i] = {roles[i].dst, roles[i].src, roles[i].src};
-      if (!stage(1, 0.5, 0.5)) return MHD_ERR_HIP;
+      if (!stage(1, 0.5, 0.5, true)) return MHD_ERR_HIP;
     } else if (integ == MHD_RK3) {
       // U_2 = 1/4 S_dt(U_1) + 3/4 U_0 into the third buffer, then
       // U^{n+1} = 2/3 S_dt(U_2) + 1/3 U_0 written over U_0 (cur is 0 here)
       for (int i = 0; i < m; ++i) roles[i] = {1, 2, 0};
-      if (!stage(1, 0.25, 0.75)) return MHD_ERR_HIP;
+      if (!stage(1, 0.25, 0.75, false)) return MHD_ERR_HIP;
       for (int i = 0; i < m; ++i) roles[i] = {2, 0, 0};
-      if (!stage(1, 2.0 / 3.0, 1.0 / 3.0)) return MHD_ERR_HIP;
+      if (!stage(1, 2.0 / 3.0, 1.0 / 3.0, true)) return MHD_ERR_HIP;
     } else {
       for (int i = 0; i < m; ++i) act[i]->cur = roles[i].dst;
+      if (launch_ctl(k_end, act, m, par, ts, st) != hipSuccess) return MHD_ERR_HIP;
     }
-    if (launch_ctl(false, act, m, ts, st) != hipSuccess) return MHD_ERR_HIP;
     for (int i = 0; i < m; ++i) act[i]->stages_valid = integ != MHD_EULER;
   }
   return MHD_OK;
@@ -897,12 +888,12 @@ int mhd_set_state(mhd_ctx* c, const mhd_state_view* v, double t, double dt_next)
     return MHD_ERR_HIP;
   if (vp) {
     const Roles r0 = {0, 0, 0};
-    if (launch_vpot(&c, &r0, 1, 0, 1.0, 0.0, false, c->stream) != hipSuccess) return MHD_ERR_HIP;
+    if (launch_vpot(&c, &r0, 1, 0, 1.0, 0.0, 0, false, c->stream) != hipSuccess) return MHD_ERR_HIP;
   }
   if (!(dt_next > 0.0)) {
     // eq. (cfl) on the initial state: the stage kernel in measuring mode
     const Roles r0 = {0, 1, 0};
-    if (launch_stage(&c, &r0, 1, 2, 1.0, 0.0, nullptr, c->stream) != hipSuccess) return MHD_ERR_HIP;
+    if (launch_stage(&c, &r0, 1, 2, 1.0, 0.0, nullptr, {}, c->stream) != hipSuccess) return MHD_ERR_HIP;
     hipLaunchKernelGGL(k_init_dt, dim3(1), dim3(1), 0, c->stream, c->sc);
     if (hipGetLastError() != hipSuccess) return MHD_ERR_HIP;
   }
@@ -1026,7 +1017,7 @@ int mhd_tune(mhd_ctx* const* ctxs, int n, int reps, void* stream, mhd_tune_resul
   // first launch warms up)
   auto time_group = [&](float* med) -> int {
     for (int r = 0; r <= reps; ++r) {
-      if (hipEventRecord(e0, st) != hipSuccess || launch_stage(ctxs, src, n, 0, 1.0, 0.0, nullptr, st) != hipSuccess ||
+      if (hipEventRecord(e0, st) != hipSuccess || launch_stage(ctxs, src, n, 0, 1.0, 0.0, nullptr, {}, st) != hipSuccess ||
           hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess)
         return MHD_ERR_HIP;
       float ms = 0.0f;
@@ -1131,8 +1122,12 @@ int mhd_tune(mhd_ctx* const* ctxs, int n, int reps, void* stream, mhd_tune_resul
     free(order);
     free(cells);
   }
-  // the timed launches wrote the second buffer
+  // the timed launches wrote the second buffer and a CFL maximum
   for (int i = 0; i < n; ++i) ctxs[i]->stages_valid = 0;
+  if ((launch_ctl(k_unmeasure, ctxs, n, 0, nullptr, st) != hipSuccess ||
+       hipStreamSynchronize(st) != hipSuccess) &&
+      rc == MHD_OK)
+    rc = MHD_ERR_HIP;
   if (rc == MHD_OK)
     for (int i = 0; i < n && rc == MHD_OK; ++i) rc = apply_shape(ctxs[i], best_tile, cls_cap[i]);
   // an automatic length depends on what is launched together: a group's is fixed as

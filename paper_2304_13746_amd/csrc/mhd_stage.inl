@@ -543,7 +543,16 @@ stage_kernel(BatchArgs ba) {
   const int xgi1 = wrapi(xgi + 1, a.nx), xgj1 = wrapi(xgj + 1, a.ny);
   const bool extra_corner = has_extra && xci >= -1 && xci <= TX && xcj >= -1 && xcj <= TY;
 
-  const double dtd = ld_agent(&a.sc->dt);
+  // the step of this cycle, and its end with the last stage (BatchArgs::first, last)
+  double dtd;
+  if (MODE == MODE_STAGE1 && ba.first) {
+    dtd = clip_step(ld_agent(&a.sc->dt_next), ld_agent(&a.sc->t), ba.t_stop[box]);
+    if (b == 0 && t == 0) st_agent(&a.scw->dt[ba.par], dtd);
+  } else {
+    dtd = ld_agent(&a.sc->dt[ba.par]);
+  }
+  if (MODE == MODE_COMBINE && ba.last && b == 0 && t == 0)
+    end_cycle(a.scw, ba.par, ba.t_stop[box]);
   const R dt = (R)dtd;
   const R tau_x = dt * a.idl[0], tau_y = dt * a.idl[1], tau_z = dt * a.idl[2];
 

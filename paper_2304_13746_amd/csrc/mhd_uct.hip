@@ -196,7 +196,7 @@ __global__ void __launch_bounds__(kUctBlock) k_uct_ct(BatchArgs ba) {
   const long long cxp = c - i + (i + 1 == nx ? 0 : i + 1);
   const long long cyp = c + (long long)((j + 1 == ny ? 0 : j + 1) - j) * nx;
   const long long czp = c + (long long)((k + 1 == nz ? 0 : k + 1) - k) * plane;
-  const R dt = (R)ld_agent(&d->sc->dt);
+  const R dt = (R)ld_agent(&d->sc->dt[ba.par]);
   const R tx = dt * (R)d->idl[0], ty = dt * (R)d->idl[1], tz = dt * (R)d->idl[2];
   const R* u = static_cast<const R*>(d->uct);
   const long long us = d->ustride;

@@ -33,7 +33,7 @@ __global__ void __launch_bounds__(kVpotBlock) k_vpot_update(BatchArgs ba) {
   const long long n = (long long)d->nx * d->ny * d->nz;
   const long long c = (long long)(blockIdx.x - ba.start[box]) * kVpotBlock + threadIdx.x;
   if (c >= n) return;
-  const double dt = ld_agent(&d->sc->dt);
+  const double dt = ld_agent(&d->sc->dt[ba.par]);
   const int si = ba.src[box], di = ba.dst[box], bi = ba.base[box];
   // the edge EMFs: in the output's face-field slots, or (edge solves) in the
   // edge-EMF scratch arrays, 12 .. 14 (UCT-HLL) or 18 .. 20 (UCT-HLLD)
