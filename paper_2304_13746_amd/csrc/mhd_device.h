@@ -26,15 +26,56 @@ struct Tol<float> {
   static constexpr float degen = 1e-6f;
 };
 
-// FP64 keeps IEEE division and square root (correctly rounded, as on the host).
-// FP32 uses the hardware reciprocal and square root (about 1 ulp), whose
-// error is far below the FP32 state's own rounding over a run.
-__device__ __forceinline__ double dsqrt(double x) { return __builtin_sqrt(x); }
+// FP64 divides and takes square roots correctly rounded, as on the host.  The compiler's
+// sequences do so for any operand: 11 instructions a quotient and 18 a root, with the
+// operands scaled away from under- and overflow and waits around the scaling flag.  They
+// were two fifths of the stage kernel's instructions.  Where the operands cannot be tiny,
+// huge or zero the iterations alone round the same way (7 and 10 instructions; with the
+// limiters and star states as selects a 256^3 cycle went from 5.45 to 4.64 ms):
+//   rcp: the hardware's estimate (relative error under 2^-24), one cubic step, then one
+//   step with the residual 1 - x y exact in an fma (Markstein 1990); exact for normal x
+//   with a normal reciprocal.  Not for 0 or infinity, which give NaN: a density, a fan
+//   width or a star denominator that is zero has no meaningful flux either way.
+//   dsqrt: Goldschmidt's coupled steps for sqrt(x) and 1 / (2 sqrt(x)), then two steps
+//   with exact residuals; exact for 2^-968 <= x < 2^1022.  dsqrt0 takes zero too.
+// dvd stays IEEE: its numerators can be as small as a field's or a velocity's tail.
+// FP32 uses the hardware reciprocal and square root (about 1 ulp), whose error is far
+// below the FP32 state's own rounding over a run.
+__device__ __forceinline__ double recip_near(double b) {
+  const double y = __builtin_amdgcn_rcp(b);
+  const double e = __builtin_fma(-b, y, 1.0);
+  return __builtin_fma(y, __builtin_fma(e, e, e), y);
+}
+// a / b from y = recip_near(b), where a, the quotient and a - b q are normal numbers
+__device__ __forceinline__ double quotient(double a, double b, double y) {
+  const double q = a * y;
+  return __builtin_fma(__builtin_fma(-b, q, a), y, q);
+}
+__device__ __forceinline__ double dsqrt(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  const double r = __builtin_fma(-h, g, 0.5);
+  h = __builtin_fma(h, r, h);
+  g = __builtin_fma(g, r, g);
+  g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+  return __builtin_fma(__builtin_fma(-g, g, x), h, g);
+}
 __device__ __forceinline__ float dsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
-__device__ __forceinline__ double rcp(double x) { return 1.0 / x; }
+__device__ __forceinline__ double dsqrt0(double x) {
+  const double g = dsqrt(x);
+  return x == 0.0 ? x : g;
+}
+__device__ __forceinline__ float dsqrt0(float x) { return __builtin_amdgcn_sqrtf(x); }
+__device__ __forceinline__ double rcp(double x) {
+  const double y = recip_near(x);
+  return __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+}
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ double dvd(double a, double b) { return a / b; }
 __device__ __forceinline__ float dvd(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
+// Quotient of normal numbers (no tails in the numerator).
+__device__ __forceinline__ double ndiv(double a, double b) { return quotient(a, b, recip_near(b)); }
+__device__ __forceinline__ float ndiv(float a, float b) { return dvd(a, b); }
 // Quotient with IEEE division in both precisions, for limiter ratios whose
 // divisor can be arbitrarily small (differences of nearly uniform data): the FP32
 // reciprocal overflows for subnormal divisors and 0 * inf is NaN, while a true
@@ -47,10 +88,21 @@ __device__ __forceinline__ float dabs(float x) { return __builtin_fabsf(x); }
 
 // van Leer slope: harmonic mean of the one-sided differences if they share a
 // sign, zero otherwise.
+//
+// FP64 forms the quotient either way: as a branch around each of a plane's 35 limiters
+// it cut the face solves into blocks too small to schedule.  The product can be as small as a number gets (the square of a tail), so it is scaled by 2^104 on the way
+// into the quotient and the slope back on the way out, both exact: the residual's last
+// place is then above 2^-1074 for every product, and differences up to 2^459 pass.
 template <typename R>
 __device__ __forceinline__ R van_leer(R dm, R dp) {
-  R s = dp * dm;
-  return s > R(0) ? dvd(R(2) * s, dp + dm) : R(0);
+  const R s = dp * dm;
+  if constexpr (sizeof(R) == 8) {
+    const R d = dp + dm;
+    const R q = quotient(s * 0x1p+105, d, recip_near(d)) * 0x1p-104;
+    return __builtin_unpredictable(s > R(0)) ? q : R(0);
+  } else {
+    return s > R(0) ? dvd(R(2) * s, dp + dm) : R(0);
+  }
 }
 
 // Reconstructions of Sec. 2.3: van Leer PLM, PPM (below), or the compact
@@ -166,8 +218,10 @@ __device__ __forceinline__ void recon_pair(R q0, R q1, R q2, R& lo, R& hi) {
   }
 }
 
-// Fast magnetosonic speed from a^2 = gamma p / rho, |B|^2 / rho and B_n^2 / rho.
-template <typename R>
+// Fast magnetosonic speed from a^2 = gamma p / rho, |B|^2 / rho and B_n^2 / rho.  ZERO: it
+// can be zero, with the negative face pressures that PPM can give (a limited face of PLM
+// or LimO3 lies between its cell and a neighbour).
+template <bool ZERO, typename R>
 __device__ __forceinline__ R fast_speed(R gamma, R rho, R p, R bn, R b1, R b2) {
   R irho = rcp(rho);
   R a2 = (gamma * p) * irho;
@@ -176,8 +230,20 @@ __device__ __forceinline__ R fast_speed(R gamma, R rho, R p, R bn, R b1, R b2) {
   R cn2 = (bn * bn) * irho;
   R s = a2 + ca2;
   R disc = s * s - R(4) * (a2 * cn2);
-  disc = disc > R(0) ? disc : R(0);
-  return dsqrt(R(0.5) * (s + dsqrt(disc)));
+  // FP64: a root of a positive number; 2^-500 in place of 0 leaves s + root at s
+  const R least = sizeof(R) == 8 ? R(0x1p-1000) : R(0);
+  disc = disc > least ? disc : least;
+  const R c2 = R(0.5) * (s + dsqrt(disc));
+  return ZERO ? dsqrt0(c2) : dsqrt(c2);
+}
+
+// Sound speed of a face without a field: what fast_speed gives there, since the root of a
+// rounded square is exact (0 where the pressure is negative).
+template <bool ZERO, typename R>
+__device__ __forceinline__ R sound_speed(R gamma, R rho, R p) {
+  const R a2 = (gamma * p) * rcp(rho);
+  const R c2 = a2 < R(0) ? R(0) : a2;
+  return ZERO ? dsqrt0(c2) : dsqrt(c2);
 }
 
 // A face-frame primitive state: (rho, v_n, v_t1, v_t2, B_t1, B_t2, p).
@@ -231,11 +297,13 @@ __device__ __forceinline__ void thermo(const Prim<R>& w, R bn, R igm1, R& e, R& 
 
 // Outer signal speeds S_L = min(v_n) - max(c_f), S_R = max(v_n) + max(c_f) and the
 // face's largest |speed| for the CFL condition.
-template <typename R>
+template <bool ZERO, bool HYDRO = false, typename R>
 __device__ __forceinline__ void outer_speeds(R gamma, const Prim<R>& l, const Prim<R>& r, R bn,
                                              R& sl, R& sr, R& cmax) {
-  R cfl = fast_speed(gamma, l.rho, l.p, bn, l.b1, l.b2);
-  R cfr = fast_speed(gamma, r.rho, r.p, bn, r.b1, r.b2);
+  R cfl = HYDRO ? sound_speed<ZERO>(gamma, l.rho, l.p)
+                : fast_speed<ZERO>(gamma, l.rho, l.p, bn, l.b1, l.b2);
+  R cfr = HYDRO ? sound_speed<ZERO>(gamma, r.rho, r.p)
+                : fast_speed<ZERO>(gamma, r.rho, r.p, bn, r.b1, r.b2);
   R cfm = cfl > cfr ? cfl : cfr;
   R umin = l.un < r.un ? l.un : r.un;
   R umax = l.un > r.un ? l.un : r.un;
@@ -246,14 +314,14 @@ __device__ __forceinline__ void outer_speeds(R gamma, const Prim<R>& l, const Pr
 }
 
 // HLL flux (one averaged state between S_L and S_R).
-template <typename R>
+template <bool ZERO, typename R>
 __device__ __forceinline__ void flux_hll(R gamma, R igm1, const Prim<R>& l, const Prim<R>& r, R bn,
                                          R* f, R& cmax) {
   Cons<R> cl, cr;
   physical(l, bn, igm1, cl);
   physical(r, bn, igm1, cr);
   R sl, sr;
-  outer_speeds(gamma, l, r, bn, sl, sr, cmax);
+  outer_speeds<ZERO>(gamma, l, r, bn, sl, sr, cmax);
   if (sl >= R(0)) {
 #pragma unroll
     for (int q = 0; q < 7; ++q) f[q] = cl.f[q];
@@ -286,20 +354,32 @@ __device__ __forceinline__ void hlld_star(const Prim<R>& w, R ea, R pta, R bn, R
   R t = da * sam;
   R bn2 = bn * bn;
   R den = t - bn2;
+  const bool flat = dabs(den) <= Tol<R>::degen * (dabs(t) + bn2);
   R v1s, v2s, b1s, b2s;
-  if (dabs(den) <= Tol<R>::degen * (dabs(t) + bn2)) {
+  auto rotated = [&] {
+    const R iden = rcp(den);
+    const R tv = (bn * (sm - w.un)) * iden;
+    const R tb = (da * sua - bn2) * iden;
+    v1s = w.v1 - w.b1 * tv;
+    v2s = w.v2 - w.b2 * tv;
+    b1s = w.b1 * tb;
+    b2s = w.b2 * tb;
+  };
+  // FP64: selects, since the rotated state is wanted nearly everywhere.  In FP32 a branch
+  // keeps the compiler from folding them into multiplications that it then contracts.
+  if constexpr (sizeof(R) == 8) {
+    rotated();
+    v1s = flat ? w.v1 : v1s;
+    v2s = flat ? w.v2 : v2s;
+    b1s = flat ? w.b1 : b1s;
+    b2s = flat ? w.b2 : b2s;
+  } else if (flat) {
     v1s = w.v1;
     v2s = w.v2;
     b1s = w.b1;
     b2s = w.b2;
   } else {
-    R iden = rcp(den);
-    R tv = (bn * (sm - w.un)) * iden;
-    R tb = (da * sua - bn2) * iden;
-    v1s = w.v1 - w.b1 * tv;
-    v2s = w.v2 - w.b2 * tv;
-    b1s = w.b1 * tb;
-    b2s = w.b2 * tb;
+    rotated();
   }
   R vba = (w.un * bn + w.v1 * w.b1) + w.v2 * w.b2;
   R vbs = (sm * bn + v1s * b1s) + v2s * b2s;
@@ -328,16 +408,31 @@ __device__ __forceinline__ Star<R> pick(bool c, const Star<R>& a, const Star<R>&
   return s;
 }
 
+// The Alfven speeds of the star states, S_M -+ |B_n| / sqrt(rho*), from the roots.  FP64
+// forms the quotients with |B_n| (which can be a tail) scaled up, and takes the scale off
+// in the fma that adds S_M: one rounding, that of S_M -+ the rounded quotient.
+template <typename R>
+__device__ __forceinline__ void alfven_speeds(R sm, R abn, R sql, R sqr, R& ssl, R& ssr) {
+  if constexpr (sizeof(R) == 8) {
+    const R a = abn * 0x1p+104;
+    ssl = __builtin_fma(quotient(a, sql, recip_near(sql)), -0x1p-104, sm);
+    ssr = __builtin_fma(quotient(a, sqr, recip_near(sqr)), 0x1p-104, sm);
+  } else {
+    ssl = sm - dvd(abn, sql);
+    ssr = sm + dvd(abn, sqr);
+  }
+}
+
 // HLLD flux: fans S_L < S*_L < S_M < S*_R < S_R.  The region is found from the
 // speeds and star densities first; then only the side whose states the flux
 // is built from (left for S*_L >= 0 or S_M >= 0 > S*_L, right otherwise) gets
 // its conserved vector and physical flux evaluated, with the same expressions
 // F*_a = F_a + S_a (U*_a - U_a) and F**_a = F*_a + S*_a (U**_a - U*_a).
-template <typename R>
+template <bool ZERO, typename R>
 __device__ __forceinline__ void flux_hlld(R gamma, R igm1, const Prim<R>& l, const Prim<R>& r, R bn,
                                           R* f, R& cmax) {
   R sl, sr;
-  outer_speeds(gamma, l, r, bn, sl, sr, cmax);
+  outer_speeds<ZERO>(gamma, l, r, bn, sl, sr, cmax);
   if (sl >= R(0) || sr <= R(0)) {  // supersonic: upwind physical flux
     Cons<R> c;
     physical(sl >= R(0) ? l : r, bn, igm1, c);
@@ -358,8 +453,8 @@ __device__ __forceinline__ void flux_hlld(R gamma, R igm1, const Prim<R>& l, con
   hlld_star(r, er, ptr, bn, sr, sm, pts, str);
   R sql = dsqrt(stl.rho), sqr = dsqrt(str.rho);
   R abn = dabs(bn);
-  R ssl = sm - dvd(abn, sql);
-  R ssr = sm + dvd(abn, sqr);
+  R ssl, ssr;
+  alfven_speeds(sm, abn, sql, sqr, ssl, ssr);
   const bool star_l = ssl >= R(0);
   const bool star_r = !star_l && !(sm >= R(0)) && !(ssr >= R(0));
   const bool dstar = !star_l && !star_r;
@@ -392,11 +487,11 @@ __device__ __forceinline__ void flux_hlld(R gamma, R igm1, const Prim<R>& l, con
 // part (zero B fluxes, no magnetic pressure, sound-speed bounds).  Contact speed
 // S* = (p_R - p_L + d_L u_L - d_R u_R) / (d_L - d_R), d_K = rho_K (S_K - u_K);
 // star state d_K/(S_K - S*) (1, S*, v1, v2, E/rho + (S* - u)(S* + p/d_K)).
-template <typename R>
+template <bool ZERO, typename R>
 __device__ __forceinline__ void flux_hllc(R gamma, R igm1, Prim<R> l, Prim<R> r, R* f, R& cmax) {
   l.b1 = l.b2 = r.b1 = r.b2 = R(0);
   R sl, sr;
-  outer_speeds(gamma, l, r, R(0), sl, sr, cmax);
+  outer_speeds<ZERO, true>(gamma, l, r, R(0), sl, sr, cmax);
   if (sl >= R(0) || sr <= R(0)) {  // supersonic: upwind physical flux
     Cons<R> c;
     physical(sl >= R(0) ? l : r, R(0), igm1, c);
@@ -413,13 +508,13 @@ __device__ __forceinline__ void flux_hllc(R gamma, R igm1, Prim<R> l, Prim<R> r,
   const R dk = left ? dl : dr;
   Cons<R> c;
   physical(w, R(0), igm1, c);
-  const R fac = dvd(dk, sk - ss);
+  const R fac = ndiv(dk, sk - ss);
   R us[7];
   us[0] = fac;
   us[1] = fac * ss;
   us[2] = fac * w.v1;
   us[3] = fac * w.v2;
-  us[4] = fac * (dvd(c.u[4], w.rho) + (ss - w.un) * (ss + dvd(w.p, dk)));
+  us[4] = fac * (ndiv(c.u[4], w.rho) + (ss - w.un) * (ss + ndiv(w.p, dk)));
   us[5] = R(0);
   us[6] = R(0);
 #pragma unroll
@@ -440,11 +535,11 @@ __device__ __forceinline__ void flux_hllc(R gamma, R igm1, Prim<R> l, Prim<R> r,
 //   **R: aL = S*_R sqL sqR / ((sqL + sqR) |B_n|), aR = 1 - aL,
 //        dL = S*_R betaL - aL u_L,
 //        dR = aR u_R - (u_R + S_R (chi_R - 1) + S*_R (betaR - chi_R)).
-template <typename R>
+template <bool ZERO, typename R>
 __device__ __forceinline__ void hlld_uct_coef(R gamma, const Prim<R>& l, const Prim<R>& r, R bn,
                                               R& al, R& ar, R& dl_, R& dr_) {
   R sl, sr, cmax;
-  outer_speeds(gamma, l, r, bn, sl, sr, cmax);
+  outer_speeds<ZERO>(gamma, l, r, bn, sl, sr, cmax);
   dl_ = R(0);
   dr_ = R(0);
   if (sl >= R(0)) {
@@ -487,8 +582,8 @@ __device__ __forceinline__ void hlld_uct_coef(R gamma, const Prim<R>& l, const P
   }
   const R sql = dsqrt(rhos[0]), sqr = dsqrt(rhos[1]);
   const R abn = dabs(bn);
-  const R ssl = sm - dvd(abn, sql);
-  const R ssr = sm + dvd(abn, sqr);
+  R ssl, ssr;
+  alfven_speeds(sm, abn, sql, sqr, ssl, ssr);
   if (ssl >= R(0)) {
     al = R(1);
     ar = R(0);
@@ -521,15 +616,15 @@ __device__ __forceinline__ void hlld_uct_coef(R gamma, const Prim<R>& l, const P
 
 enum { SOLVER_HLLD = 0, SOLVER_HLL = 1, SOLVER_HLLC = 2 };
 
-template <int SOLVER, typename R>
+template <int SOLVER, bool ZERO, typename R>
 __device__ __forceinline__ void riemann(R gamma, R igm1, const Prim<R>& l, const Prim<R>& r, R bn,
                                         R* f, R& cmax) {
   if constexpr (SOLVER == SOLVER_HLL)
-    flux_hll(gamma, igm1, l, r, bn, f, cmax);
+    flux_hll<ZERO>(gamma, igm1, l, r, bn, f, cmax);
   else if constexpr (SOLVER == SOLVER_HLLC)
-    flux_hllc(gamma, igm1, l, r, f, cmax);
+    flux_hllc<ZERO>(gamma, igm1, l, r, f, cmax);
   else
-    flux_hlld(gamma, igm1, l, r, bn, f, cmax);
+    flux_hlld<ZERO>(gamma, igm1, l, r, bn, f, cmax);
 }
 
 // Corner-EMF schemes of Sec. 2.4 (Gardiner & Stone 2005): E^c upwinds the
@@ -542,7 +637,13 @@ enum { EMF_EC = 0, EMF_E0 = 1, EMF_ARITH = 2, EMF_UCT = 3, EMF_UCT_HLLD = 4 };
 // Upwind choice by the sign of a mass flux; zero averages the two candidates.
 template <typename R>
 __device__ __forceinline__ R upwind(R s, R l, R r) {
-  return s > R(0) ? l : (s < R(0) ? r : R(0.5) * (l + r));
+  if constexpr (sizeof(R) == 8) {  // without branches
+    const R m = R(0.5) * (l + r);
+    const R d = s < R(0) ? r : m;
+    return s > R(0) ? l : d;
+  } else {
+    return s > R(0) ? l : (s < R(0) ? r : R(0.5) * (l + r));
+  }
 }
 
 // E^c corner EMF in the (P, Q) plane at (p-1/2, q-1/2) (Gardiner & Stone 2005):

@@ -200,12 +200,12 @@ struct Face {
 };
 
 // UCT = 0: no edge-solve data; EMF_UCT (UCT-HLL) or EMF_UCT_HLLD
-template <int D, int SOLVER, int UCT = 0, typename R>
+template <int D, int SOLVER, int UCT, bool ZERO, typename R>
 __device__ __forceinline__ void solve_face(const StageArgs<R>& a, const R* ql, const R* qr, R bn,
                                            Face<R>& out) {
   R f[7];
   const Prim<R> l = as_prim(ql), r = as_prim(qr);
-  riemann<SOLVER>(a.gamma, a.igm1, l, r, bn, f, out.cmax);
+  riemann<SOLVER, ZERO>(a.gamma, a.igm1, l, r, bn, f, out.cmax);
   to_grid<D>(f, out.cons);
   out.fb1 = f[5];
   out.fb2 = f[6];
@@ -213,7 +213,7 @@ __device__ __forceinline__ void solve_face(const StageArgs<R>& a, const R* ql, c
     // alpha+ = max(0, S_R), alpha- = max(0, -S_L) of the outer bounds and the
     // transverse velocities averaged with the HLL weights
     R sl, sr, cm;
-    outer_speeds(a.gamma, l, r, bn, sl, sr, cm);
+    outer_speeds<ZERO>(a.gamma, l, r, bn, sl, sr, cm);
     const R ap = sr > R(0) ? sr : R(0);
     const R am = sl < R(0) ? -sl : R(0);
     out.ap = ap;
@@ -222,7 +222,7 @@ __device__ __forceinline__ void solve_face(const StageArgs<R>& a, const R* ql, c
     out.vt2 = dvd(ap * l.v2 + am * r.v2, ap + am);
   } else if constexpr (UCT == EMF_UCT_HLLD) {
     // the HLLD coefficients and the transverse velocities they weight
-    hlld_uct_coef(a.gamma, l, r, bn, out.ap, out.am, out.dl, out.dr);
+    hlld_uct_coef<ZERO>(a.gamma, l, r, bn, out.ap, out.am, out.dl, out.dr);
     out.vt1 = out.ap * l.v1 + out.am * r.v1;
     out.vt2 = out.ap * l.v2 + out.am * r.v2;
   }
@@ -444,7 +444,8 @@ template <typename R, int SOLVER, int RECON, int EMF, int CT, int MODE, int TX, 
 __global__ void __launch_bounds__(TX * TY + 2 * (TX + TY))
 __attribute__((amdgpu_waves_per_eu(Occupancy<R, SOLVER == SOLVER_HLLC, RECON == RECON_PPM>::waves)))
 stage_kernel(BatchArgs ba) {
-  constexpr int H = RECON == RECON_PPM ? 3 : 2;
+  constexpr bool PPM = RECON == RECON_PPM;
+  constexpr int H = PPM ? 3 : 2;
   constexpr int NS = 2 * H;  // cells a face's two states read along its direction
   using T = Tile<TX, TY, H>;
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -467,6 +468,7 @@ stage_kernel(BatchArgs ba) {
   constexpr int NB = LdsLayout<R, TX, TY, HY, H, DD>::NB;
   SA_t& SA = *reinterpret_cast<SA_t*>(smem_raw);
   auto& S = SA.s;
+  constexpr bool EL = sizeof(R) == 8 && NB == 2;  // own EMFs of the plane before kept in LDS only
   constexpr bool CL = Carry<R, TX, TY>::in_lds;
   constexpr bool PF = sizeof(R) == 4 && RECON != RECON_PPM;  // next-plane prefetch (below)
 
@@ -564,7 +566,6 @@ stage_kernel(BatchArgs ba) {
   R top7[7];
   // PPM reaches two planes each way: the z-frame of plane m-2 and the
   // primitives of plane m+1 (read one iteration ahead) join the window
-  constexpr bool PPM = RECON == RECON_PPM;
   R zm2[PPM ? 7 : 1];
   Cell<R> wn;
   // FP64 PPM also carries the interface value at (m-1/2) from one cell to the
@@ -748,7 +749,7 @@ stage_kernel(BatchArgs ba) {
           bn = gld(a.src[5], (long long)km * plane + col);
         }
       }
-      solve_face<0, SOLVER, UK>(a, ql, qr, bn, fx);
+      solve_face<0, SOLVER, UK, PPM>(a, ql, qr, bn, fx);
       // the previous plane's exports were consumed before the last barrier
       if constexpr (NE) {
 #pragma unroll
@@ -800,7 +801,7 @@ stage_kernel(BatchArgs ba) {
           bn = gld(a.src[6], (long long)km * plane + col);
         }
       }
-      solve_face<1, SOLVER, UK>(a, ql, qr, bn, fy);
+      solve_face<1, SOLVER, UK, PPM>(a, ql, qr, bn, fy);
       if constexpr (NE) {
 #pragma unroll
         for (int q = 0; q < 5; ++q) S.ycons[q][ex_me] = fy.cons[q];
@@ -902,7 +903,7 @@ stage_kernel(BatchArgs ba) {
           qa[v] = hi;  // becomes top of cell m
         }
       }
-      if (m >= z0) solve_face<2, SOLVER, UK>(a, top7, bot, bz_m, fz);
+      if (m >= z0) solve_face<2, SOLVER, UK, PPM>(a, top7, bot, bz_m, fz);
       if constexpr (UCT) {
         if (real && m >= z0 && m < z1) put_uct<2, UK>(a, (long long)km * plane + col, fz);
       }
@@ -918,6 +919,12 @@ stage_kernel(BatchArgs ba) {
     const R erz = w0.vy * w0.bx - w0.vx * w0.by;
     if (real && m >= z0 && m < z1) bad |= bad_cell(w0);
 
+    // FP64 reads its own EMFs of the plane before back from LDS, here and below, instead
+    // of carrying them in registers that the face solves would spill (1.6 % at 256^3)
+    if constexpr (!NE && EL) {
+      erx_prev = S.erx[ex_me];
+      ery_prev = S.ery[ex_me];
+    }
     if constexpr (!NE) {
       S.zex[ex_me] = fz.fb2;
       S.zey[ex_me] = -fz.fb1;
@@ -980,6 +987,10 @@ stage_kernel(BatchArgs ba) {
         R cy = S.ycmax[ex_me] > S.ycmax[e_n] ? S.ycmax[ex_me] : S.ycmax[e_n];
         cxy_new = cx * a.idl[0] + cy * a.idl[1];
       }
+    }
+    if constexpr (!NE && EL) {
+      ex_prev = S.ex[pm1][ex_me];
+      ey_prev = S.ey[pm1][ex_me];
     }
     // finalise cell m-1: z-flux difference, stage combination, face B
     if (real && m - 1 >= z0 && m <= z1) {
@@ -1065,10 +1076,12 @@ stage_kernel(BatchArgs ba) {
     xmass_prev = xmass_now;
     yex_prev = yex_now;
     ymass_prev = ymass_now;
-    erx_prev = erx;
-    ery_prev = ery;
-    ex_prev = ex_new;
-    ey_prev = ey_new;
+    if constexpr (!EL) {
+      erx_prev = erx;
+      ery_prev = ery;
+      ex_prev = ex_new;
+      ey_prev = ey_new;
+    }
     if (extra_corner) erz_extra = wx.vy * wx.bx - wx.vx * wx.by;
     // the LDS plane now holds plane m+1 (written in B)
   }
