@@ -951,6 +951,32 @@ stage_kernel(BatchArgs ba) {
     // comes first: after C without corner EMFs or with one EMF plane, after D
     // with them)
 
+    // FP32: what the update of plane m-1 reads from memory, ahead of the corner EMFs whose
+    // branches the compiler does not move loads across
+    constexpr bool PU = sizeof(R) == 4 && MODE != MODE_MEASURE;
+    constexpr bool FB = !NE && CT == CT_FACE;  // the face field is updated here
+    const long long ou = (long long)wrapi(m - 1, a.nz) * plane + col;
+    R u0[PU && MODE == MODE_COMBINE ? 5 : 1], bs[PU && FB ? 2 : 1], b0[PU && FB && MODE == MODE_COMBINE ? 3 : 1];
+    if constexpr (PU) {
+      if (real && m - 1 >= z0) {
+        if constexpr (FB) {
+          bs[0] = gld(a.src[5], ou);
+          bs[1] = gld(a.src[6], ou);
+        }
+        if constexpr (MODE == MODE_COMBINE) {
+#pragma unroll
+          for (int q = 0; q < 5; ++q) u0[q] = gld<R>(a.dst[q], ou + a.boff);
+          if constexpr (FB) {
+            b0[0] = gld<R>(a.dst[5], ou + a.boff);
+            b0[1] = gld<R>(a.dst[6], ou + a.boff);
+          }
+        }
+      }
+      if constexpr (FB && MODE == MODE_COMBINE) {
+        if (real && m >= z0 && m < z1) b0[2] = gld<R>(a.dst[7], (long long)km * plane + col + a.boff);
+      }
+    }
+
     // ---------------- C: corner EMFs, cell update of plane m-1
     R ez_new = 0, ex_new = 0, ey_new = 0;
     if constexpr (!NE) {
@@ -1006,7 +1032,7 @@ stage_kernel(BatchArgs ba) {
         for (int q = 0; q < 5; ++q) un[q] = pt_(q) - tau_z * (fz.cons[q] - fzp(q));
         if constexpr (MODE == MODE_COMBINE) {
 #pragma unroll
-          for (int q = 0; q < 5; ++q) un[q] = a.w * un[q] + a.w0 * gld<R>(a.dst[q], o + a.boff);
+          for (int q = 0; q < 5; ++q) un[q] = a.w * un[q] + a.w0 * (PU ? u0[PU ? q : 0] : gld<R>(a.dst[q], o + a.boff));
         }
 #pragma unroll
         for (int q = 0; q < 5; ++q) gst(a.dst[q], o, un[q]);
@@ -1017,11 +1043,11 @@ stage_kernel(BatchArgs ba) {
           // the face field is updated after the edge solve
         } else if constexpr (CT == CT_FACE) {
           const int e_e = T::e(ci + 1, cj), e_n = T::e(ci, cj + 1);
-          R bxn = (gld(a.src[5], o) - tau_y * (S.ez[pm1][e_n] - S.ez[pm1][ex_me])) + tau_z * (ey_new - ey_prev);
-          R byn = (gld(a.src[6], o) - tau_z * (ex_new - ex_prev)) + tau_x * (S.ez[pm1][e_e] - S.ez[pm1][ex_me]);
+          R bxn = ((PU ? bs[0] : gld(a.src[5], o)) - tau_y * (S.ez[pm1][e_n] - S.ez[pm1][ex_me])) + tau_z * (ey_new - ey_prev);
+          R byn = ((PU ? bs[PU ? 1 : 0] : gld(a.src[6], o)) - tau_z * (ex_new - ex_prev)) + tau_x * (S.ez[pm1][e_e] - S.ez[pm1][ex_me]);
           if constexpr (MODE == MODE_COMBINE) {
-            bxn = a.w * bxn + a.w0 * gld<R>(a.dst[5], o + a.boff);
-            byn = a.w * byn + a.w0 * gld<R>(a.dst[6], o + a.boff);
+            bxn = a.w * bxn + a.w0 * (PU ? b0[0] : gld<R>(a.dst[5], o + a.boff));
+            byn = a.w * byn + a.w0 * (PU ? b0[PU ? 1 : 0] : gld<R>(a.dst[6], o + a.boff));
           }
           gst(a.dst[5], o, bxn);
           gst(a.dst[6], o, byn);
@@ -1051,7 +1077,7 @@ stage_kernel(BatchArgs ba) {
         } else if constexpr (CT == CT_FACE) {
           const int e_e = T::e(ci + 1, cj), e_n = T::e(ci, cj + 1);
           R bzn = (bz_m - tau_x * (S.ey[pm][e_e] - ey_new)) + tau_y * (S.ex[pm][e_n] - ex_new);
-          if constexpr (MODE == MODE_COMBINE) bzn = a.w * bzn + a.w0 * gld<R>(a.dst[7], o + a.boff);
+          if constexpr (MODE == MODE_COMBINE) bzn = a.w * bzn + a.w0 * (PU ? b0[PU ? 2 : 0] : gld<R>(a.dst[7], o + a.boff));
           gst(a.dst[7], o, bzn);
         } else {
           // vector-potential form: leave this column's three corner EMFs of
