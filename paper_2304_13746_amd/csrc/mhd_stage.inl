@@ -717,7 +717,9 @@ stage_kernel(BatchArgs ba) {
     }
     // ---------------- A: x- and y-faces of plane m from the LDS plane
     Face<R> fx = {}, fy = {};
-    if (do_x || corner_x) {
+    // without corner EMFs the planes before and after the chunk lend it only their cells
+    const bool faces = !NE || (m >= z0 && m < z1);
+    if (faces && (do_x || corner_x)) {
       const int fi = corner_x ? TX : ci, fj = corner_x ? -1 : cj;
       R ql[7], qr[7];
       if constexpr (DD) {
@@ -769,7 +771,7 @@ stage_kernel(BatchArgs ba) {
         S.xcmax[ex_me] = fx.cmax;
       }
     }
-    if (do_y || corner_y) {
+    if (faces && (do_y || corner_y)) {
       const int fi = corner_y ? -1 : ci, fj = corner_y ? TY : cj;
       R ql[7], qr[7];
       if constexpr (DD) {
