@@ -200,11 +200,16 @@ struct Face {
 };
 
 // UCT = 0: no edge-solve data; EMF_UCT (UCT-HLL) or EMF_UCT_HLLD
-template <int D, int SOLVER, int UCT, bool ZERO, typename R>
+template <int D, int SOLVER, int UCT, bool ZERO, bool SPEED, typename R>
 __device__ __forceinline__ void solve_face(const StageArgs<R>& a, const R* ql, const R* qr, R bn,
                                            Face<R>& out) {
   R f[7];
   const Prim<R> l = as_prim(ql), r = as_prim(qr);
+  if constexpr (SPEED) {  // the signal speed only
+    R sl, sr;
+    outer_speeds<ZERO, SOLVER == SOLVER_HLLC>(a.gamma, l, r, bn, sl, sr, out.cmax);
+    return;
+  }
   riemann<SOLVER, ZERO>(a.gamma, a.igm1, l, r, bn, f, out.cmax);
   to_grid<D>(f, out.cons);
   out.fb1 = f[5];
@@ -355,6 +360,14 @@ struct SmemHydro {
   R ycons[5][T::NE], ycmax[T::NE];
 };
 
+// The measuring layout: primitives and the faces' signal speeds.
+template <typename R, int TX, int TY, int H, bool HY>
+struct SmemSpeed {
+  using T = Tile<TX, TY, H>;
+  R w[HY ? 5 : 8][T::NW];
+  R xcmax[T::NE], ycmax[T::NE];
+};
+
 // PPM face values limited once per cell (the FP64 PPM path): the upper x- and
 // y-face values of every column and ring corner, and the lower faces of the two
 // ring corners whose faces the tile solves.
@@ -366,19 +379,20 @@ struct SmemPPM {
 };
 struct NoSmem {};
 
-template <typename R, int TX, int TY, bool HY, int H, bool DD = false, int NB = 1>
+template <typename R, int TX, int TY, bool HY, int H, bool DD, bool MS, int NB>
 struct SmemAll {
-  std::conditional_t<HY, SmemHydro<R, TX, TY, H>, Smem<R, TX, TY, H, NB>> s;
-  Carry<R, TX, TY> c;
+  std::conditional_t<MS, SmemSpeed<R, TX, TY, H, HY>,
+                     std::conditional_t<HY, SmemHydro<R, TX, TY, H>, Smem<R, TX, TY, H, NB>>> s;
+  std::conditional_t<MS, Carry<float, TX, TY>, Carry<R, TX, TY>> c;  // nothing to carry when measuring
   std::conditional_t<DD, SmemPPM<R, TX, TY>, NoSmem> p;
 };
 
 // The layout a kernel instance uses: two corner-EMF planes unless that takes
 // the block past the 160 KiB of LDS a CU has (FP64 PPM on the 16x16 tile).
-template <typename R, int TX, int TY, bool HY, int H, bool DD>
+template <typename R, int TX, int TY, bool HY, int H, bool DD, bool MS>
 struct LdsLayout {
-  static constexpr int NB = sizeof(SmemAll<R, TX, TY, HY, H, DD, 2>) <= 160 * 1024 ? 2 : 1;
-  using type = SmemAll<R, TX, TY, HY, H, DD, NB>;
+  static constexpr int NB = sizeof(SmemAll<R, TX, TY, HY, H, DD, MS, 2>) <= 160 * 1024 ? 2 : 1;
+  using type = SmemAll<R, TX, TY, HY, H, DD, MS, NB>;
 };
 
 // Face-frame variable v of direction D (0: x, 1: y) of LDS cell iw, for a
@@ -433,16 +447,17 @@ __device__ __forceinline__ void get_cell(const SM& S, int iw, Cell<R>& c) {
 // FP64 PPM holds two more planes of its z-window in registers: the hydrodynamic
 // path keeps the MHD path's two waves, and the MHD path, whose wider LDS halo
 // leaves room for one block per CU only, takes the whole register file.
-template <typename R, bool HY, bool PPM>
+// Measuring needs no fluxes and, but for FP64 PPM, fits one wave more again.
+template <typename R, bool HY, bool PPM, bool MS>
 struct Occupancy {
-  static constexpr int waves = sizeof(R) == 4 ? MHD_WAVES_F32 + (HY ? 1 : 0)
+  static constexpr int waves = sizeof(R) == 4 ? MHD_WAVES_F32 + (HY || MS ? 1 : 0)
                                : PPM          ? (HY ? MHD_WAVES_F64 : 1)
-                                              : MHD_WAVES_F64 + (HY ? 1 : 0);
+                                              : MHD_WAVES_F64 + (HY || MS ? 1 : 0);
 };
 
 template <typename R, int SOLVER, int RECON, int EMF, int CT, int MODE, int TX, int TY>
 __global__ void __launch_bounds__(TX * TY + 2 * (TX + TY))
-__attribute__((amdgpu_waves_per_eu(Occupancy<R, SOLVER == SOLVER_HLLC, RECON == RECON_PPM>::waves)))
+__attribute__((amdgpu_waves_per_eu(Occupancy<R, SOLVER == SOLVER_HLLC, RECON == RECON_PPM, MODE == MODE_MEASURE>::waves)))
 stage_kernel(BatchArgs ba) {
   constexpr bool PPM = RECON == RECON_PPM;
   constexpr int H = PPM ? 3 : 2;
@@ -458,18 +473,21 @@ stage_kernel(BatchArgs ba) {
   // face data they need and, like the hydrodynamic path, does no corner-EMF work
   // and solves only the faces the tile's own cells need (it leaves B alone)
   constexpr bool UCT = EMF == EMF_UCT || EMF == EMF_UCT_HLLD;
-  constexpr int UK = UCT ? EMF : 0;  // which edge solve's face data to export
-  constexpr bool NE = HY || UCT;
+  constexpr int UK = UCT && MODE != MODE_MEASURE ? EMF : 0;  // which edge solve's face data to export
+  // measuring eq. (cfl) takes the faces' signal speeds alone: no flux, EMF or update
+  // (a 256^3 pass 2.57 -> 0.89 ms in FP64, 0.83 -> 0.43 in FP32)
+  constexpr bool MS = MODE == MODE_MEASURE;
+  constexpr bool NE = HY || UCT || MS;
   // FP64 PPM limits each cell's x and y faces once per plane into LDS (FP32 PPM
   // limits them per face: the extra 15 KB of LDS would cost it a block per CU,
   // measured 20 % slower)
   constexpr bool DD = RECON == RECON_PPM && sizeof(R) == 8;
-  using SA_t = typename LdsLayout<R, TX, TY, HY, H, DD>::type;
-  constexpr int NB = LdsLayout<R, TX, TY, HY, H, DD>::NB;
+  using SA_t = typename LdsLayout<R, TX, TY, HY, H, DD, MS>::type;
+  constexpr int NB = LdsLayout<R, TX, TY, HY, H, DD, MS>::NB;
   SA_t& SA = *reinterpret_cast<SA_t*>(smem_raw);
   auto& S = SA.s;
   constexpr bool EL = sizeof(R) == 8 && NB == 2;  // own EMFs of the plane before kept in LDS only
-  constexpr bool CL = Carry<R, TX, TY>::in_lds;
+  constexpr bool CL = Carry<R, TX, TY>::in_lds && !MS;
   constexpr bool PF = sizeof(R) == 4 && RECON != RECON_PPM;  // next-plane prefetch (below)
 
   // XCD-aware order: the hardware deals blocks round-robin over 8 XCDs; give
@@ -751,13 +769,14 @@ stage_kernel(BatchArgs ba) {
           bn = gld(a.src[5], (long long)km * plane + col);
         }
       }
-      solve_face<0, SOLVER, UK, PPM>(a, ql, qr, bn, fx);
+      solve_face<0, SOLVER, UK, PPM, MS>(a, ql, qr, bn, fx);
       // the previous plane's exports were consumed before the last barrier
       if constexpr (NE) {
 #pragma unroll
-        for (int q = 0; q < 5; ++q) S.xcons[q][ex_me] = fx.cons[q];
+        for (int q = 0; q < 5; ++q)
+          if constexpr (!MS) S.xcons[q][ex_me] = fx.cons[q];
         S.xcmax[ex_me] = fx.cmax;
-        if constexpr (UCT) {
+        if constexpr (UK != 0) {
           if (real && m >= z0 && m < z1) put_uct<0, UK>(a, (long long)km * plane + col, fx);
         }
       } else if (corner_x) {
@@ -803,12 +822,13 @@ stage_kernel(BatchArgs ba) {
           bn = gld(a.src[6], (long long)km * plane + col);
         }
       }
-      solve_face<1, SOLVER, UK, PPM>(a, ql, qr, bn, fy);
+      solve_face<1, SOLVER, UK, PPM, MS>(a, ql, qr, bn, fy);
       if constexpr (NE) {
 #pragma unroll
-        for (int q = 0; q < 5; ++q) S.ycons[q][ex_me] = fy.cons[q];
+        for (int q = 0; q < 5; ++q)
+          if constexpr (!MS) S.ycons[q][ex_me] = fy.cons[q];
         S.ycmax[ex_me] = fy.cmax;
-        if constexpr (UCT) {
+        if constexpr (UK != 0) {
           if (real && m >= z0 && m < z1) put_uct<1, UK>(a, (long long)km * plane + col, fy);
         }
       } else if (corner_y) {
@@ -905,8 +925,8 @@ stage_kernel(BatchArgs ba) {
           qa[v] = hi;  // becomes top of cell m
         }
       }
-      if (m >= z0) solve_face<2, SOLVER, UK, PPM>(a, top7, bot, bz_m, fz);
-      if constexpr (UCT) {
+      if (m >= z0) solve_face<2, SOLVER, UK, PPM, MS>(a, top7, bot, bz_m, fz);
+      if constexpr (UK != 0) {
         if (real && m >= z0 && m < z1) put_uct<2, UK>(a, (long long)km * plane + col, fz);
       }
 #pragma unroll
@@ -1008,8 +1028,10 @@ stage_kernel(BatchArgs ba) {
       const int e_e = T::e(ci + 1, cj), e_n = T::e(ci, cj + 1);
 #pragma unroll
       for (int q = 0; q < 5; ++q)
-        part_new[q] = (gld(a.src[q], (long long)km * plane + col) - tau_x * (S.xcons[q][e_e] - S.xcons[q][ex_me])) -
-                      tau_y * (S.ycons[q][e_n] - S.ycons[q][ex_me]);
+        if constexpr (!MS)
+          part_new[q] =
+              (gld(a.src[q], (long long)km * plane + col) - tau_x * (S.xcons[q][e_e] - S.xcons[q][ex_me])) -
+              tau_y * (S.ycons[q][e_n] - S.ycons[q][ex_me]);
       if constexpr (MODE != MODE_COMBINE) {
         R cx = S.xcmax[ex_me] > S.xcmax[e_e] ? S.xcmax[ex_me] : S.xcmax[e_e];
         R cy = S.ycmax[ex_me] > S.ycmax[e_n] ? S.ycmax[ex_me] : S.ycmax[e_n];
@@ -1095,8 +1117,10 @@ stage_kernel(BatchArgs ba) {
     // ---------------- shift the march registers
 #pragma unroll
     for (int q = 0; q < 5; ++q) {
-      pt_(q) = part_new[q];
-      fzp(q) = fz.cons[q];
+      if constexpr (!MS) {
+        pt_(q) = part_new[q];
+        fzp(q) = fz.cons[q];
+      }
     }
     zc_prev = fz.cmax;
     cxy_prev = cxy_new;
@@ -1149,7 +1173,7 @@ static hipError_t launch_one(const BatchArgs& ba, hipStream_t st, bool prepare) 
   using T = Tile<TX, TY>;
   const size_t lds =
       sizeof(typename LdsLayout<R, TX, TY, SOLVER == SOLVER_HLLC, RECON == RECON_PPM ? 3 : 2,
-                                RECON == RECON_PPM && sizeof(R) == 8>::type);
+                                RECON == RECON_PPM && sizeof(R) == 8, MODE == MODE_MEASURE>::type);
   auto fn = stage_kernel<R, SOLVER, RECON, EMF, CT, MODE, TX, TY>;
   if (prepare)
     return hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
