@@ -31,6 +31,7 @@ struct mhd_ctx {
   BoxDesc* desc;     // device copy of this box's descriptor
   double* diag_part; // per-block diagnostic partials
   int tile, zchunk;  // launch shape as requested (zchunk 0 = automatic)
+  bool shaped;       // tile or zchunk was requested: march, whatever the size
   int lz;            // z-planes per work-group: as requested, or when stepped alone
   int cols;          // x-y tiles of the box
   int diag_blocks;
@@ -492,6 +493,28 @@ double launch_cost(const mhd_params* p, long long blocks, int lz) {
   return (lz + kHead) * (full * (1.0 + share * (r - 1)) + (rest ? 1.0 + share * (rest - 1) : 0.0));
 }
 
+long long bricks(const mhd_params* p, const BrickShape& b) {
+  return (long long)((p->nx + b.x - 1) / b.x) * ((p->ny + b.y - 1) / b.y) * ((p->nz + b.z - 1) / b.z);
+}
+
+// Bricks for the stages of n contexts launched together: FP64, the default scheme, no
+// launch shape asked for, and a CU for every brick, of the smaller shape if that still
+// holds.  On the other side of that line a second round of bricks starts: 32^3 (256
+// bricks of 8x4x4) takes 38 us a cycle and marches in 58, 48^3 (864) takes 118 and
+// marches in 89; 16^3 takes 20 us as 128 bricks of 4x4x2, 29 as 32 of 8x4x4.
+int plan_brick(mhd_ctx* const* c, int n) {
+  const mhd_params* p = &c[0]->p;
+  if (p->precision != MHD_FP64 || p->recon != MHD_PLM || p->emf != MHD_EMF_EC || p->ct != MHD_CT_FACE)
+    return BRICK_NONE;
+  long long big = 0, small = 0;
+  for (int i = 0; i < n; ++i) {
+    if (c[i]->shaped) return BRICK_NONE;
+    big += bricks(&c[i]->p, kBrick[BRICK_844]);
+    small += bricks(&c[i]->p, kBrick[BRICK_442]);
+  }
+  return small <= kCus ? BRICK_442 : big <= kCus ? BRICK_844 : BRICK_NONE;
+}
+
 // The lz of n contexts launched together (n <= kMaxBatch): the requested one, or one
 // common length for all the automatic ones.
 void plan_lz(mhd_ctx* const* c, int n, short* lz) {
@@ -522,15 +545,16 @@ void plan_lz(mhd_ctx* const* c, int n, short* lz) {
 }
 
 // One stage launch over n contexts sharing precision, solver and tile, with
-// weights (w, w0) for a combining stage and lz[i] planes per block of context i
-// (null: planned here).  Batches beyond kMaxBatch go out in chunks.
+// weights (w, w0) for a combining stage, lz[i] planes per block of context i and
+// brick[j] for the j-th chunk of the batch (null: planned here).  Batches beyond
+// kMaxBatch go out in chunks.
 struct Control {
   int par, first, last;   // as in BatchArgs
   const double* t_stop;   // per context
 };
 
 hipError_t launch_stage(mhd_ctx* const* c, const Roles* r, int n, int mode, double w, double w0,
-                        const short* lz, const Control& ctl, hipStream_t st) {
+                        const short* lz, const unsigned char* brick, const Control& ctl, hipStream_t st) {
   for (int i0 = 0; i0 < n; i0 += kMaxBatch) {
     const int m = n - i0 < kMaxBatch ? n - i0 : kMaxBatch;
     BatchArgs ba = {};
@@ -544,10 +568,13 @@ hipError_t launch_stage(mhd_ctx* const* c, const Roles* r, int n, int mode, doub
     ba.first = ctl.first;
     ba.last = ctl.last;
     if (ctl.t_stop) memcpy(ba.t_stop, ctl.t_stop + i0, sizeof(double) * m);
-    if (lz)
+    if (lz) {
       memcpy(ba.lz, lz + i0, sizeof(short) * m);
-    else
+      ba.brick = brick[i0 / kMaxBatch];
+    } else {
       plan_lz(c + i0, m, ba.lz);
+      ba.brick = mode != 2 ? plan_brick(c + i0, m) : BRICK_NONE;  // measuring marches
+    }
     int g = 0;
     for (int i = 0; i < m; ++i) {
       const mhd_ctx* ci = c[i0 + i];
@@ -556,7 +583,8 @@ hipError_t launch_stage(mhd_ctx* const* c, const Roles* r, int n, int mode, doub
       ba.src[i] = r[i0 + i].src;
       ba.dst[i] = r[i0 + i].dst;
       ba.base[i] = r[i0 + i].base;
-      g += (int)ci->cols * chunks(ci->p.nz, ba.lz[i]);
+      g += ba.brick != BRICK_NONE ? (int)bricks(&ci->p, kBrick[ba.brick])
+                                  : (int)ci->cols * chunks(ci->p.nz, ba.lz[i]);
     }
     ba.start[m] = g;
     ba.total = g;
@@ -661,6 +689,7 @@ int step_group(mhd_ctx* const* c, const int* nsteps, int n, const double* t_stop
   static thread_local Roles roles[4096];
   static thread_local double ts[4096];
   static thread_local short lz[4096];
+  static thread_local unsigned char brick[4096 / kMaxBatch];
   int m = 0;
   const int integ = c[0]->p.integrator;
   const bool vp = c[0]->p.ct == MHD_CT_VECPOT;
@@ -672,7 +701,11 @@ int step_group(mhd_ctx* const* c, const int* nsteps, int n, const double* t_stop
     for (int i = 0; i < n; ++i)
       if (nsteps[i] > cyc) { act[m] = c[i]; ts[m] = t_stop ? t_stop[i] : 0.0; ++m; }
     if (cyc == 0 || m != was)  // boxes only ever leave
-      for (int i = 0; i < m; i += kMaxBatch) plan_lz(act + i, m - i < kMaxBatch ? m - i : kMaxBatch, lz + i);
+      for (int i = 0; i < m; i += kMaxBatch) {
+        const int k = m - i < kMaxBatch ? m - i : kMaxBatch;
+        plan_lz(act + i, k, lz + i);
+        brick[i / kMaxBatch] = (unsigned char)plan_brick(act + i, k);
+      }
     // stage 1: U_1 = S_dt(U_0), measuring the next dt (eq. cfl)
     for (int i = 0; i < m; ++i) {
       const int u0 = act[i]->cur;
@@ -684,7 +717,7 @@ int step_group(mhd_ctx* const* c, const int* nsteps, int n, const double* t_stop
     const int par = cyc & 1;
     auto stage = [&](int mode, double w, double w0, bool last) -> bool {
       const Control ctl = {par, cyc == 0 && mode == 0, last, ts};
-      if (launch_stage(act, roles, m, mode, w, w0, lz, ctl, st) != hipSuccess) return false;
+      if (launch_stage(act, roles, m, mode, w, w0, lz, brick, ctl, st) != hipSuccess) return false;
       if (uct && launch_uct(act, roles, m, mode, w, w0, par, !vp, st) != hipSuccess) return false;
       return !vp || launch_vpot(act, roles, m, mode, w, w0, par, true, st) == hipSuccess;
     };
@@ -712,7 +745,7 @@ int step_group(mhd_ctx* const* c, const int* nsteps, int n, const double* t_stop
 // Give c the launch shape (tile, zchunk; 0 = automatic): raise the dynamic-LDS
 // limit of the tile's kernels and rewrite the box descriptor on the device.
 // Synchronous: kernels in flight on c's stream may still read the old one.
-int apply_shape(mhd_ctx* c, int tile, int zchunk) {
+int apply_shape(mhd_ctx* c, int tile, int zchunk, bool shaped) {
   int tx, ty;
   if (!tile_dims(tile, &tx, &ty)) return MHD_ERR_INVALID_ARG;
   const mhd_params* p = &c->p;
@@ -743,6 +776,7 @@ int apply_shape(mhd_ctx* c, int tile, int zchunk) {
     return MHD_ERR_HIP;
   c->tile = tile;
   c->zchunk = zchunk;
+  c->shaped = shaped;
   c->cols = (int)columns(p, tile);
   c->lz = zchunk < p->nz ? zchunk : p->nz;
   if (zchunk == 0) {
@@ -857,7 +891,7 @@ int mhd_create(const mhd_params* p, mhd_ctx** out) {
   // a cell per thread, up to two blocks a CU
   const long long db = (c->ncell + kDiagThreads - 1) / kDiagThreads;
   c->diag_blocks = (int)(db < kDiagBlocks ? db : kDiagBlocks);
-  if (apply_shape(c, tile, p->zchunk) != MHD_OK) {
+  if (apply_shape(c, tile, p->zchunk, p->tile != 0 || p->zchunk != 0) != MHD_OK) {
     free(c);
     return MHD_ERR_HIP;
   }
@@ -893,7 +927,7 @@ int mhd_set_state(mhd_ctx* c, const mhd_state_view* v, double t, double dt_next)
   if (!(dt_next > 0.0)) {
     // eq. (cfl) on the initial state: the stage kernel in measuring mode
     const Roles r0 = {0, 1, 0};
-    if (launch_stage(&c, &r0, 1, 2, 1.0, 0.0, nullptr, {}, c->stream) != hipSuccess) return MHD_ERR_HIP;
+    if (launch_stage(&c, &r0, 1, 2, 1.0, 0.0, nullptr, nullptr, {}, c->stream) != hipSuccess) return MHD_ERR_HIP;
     hipLaunchKernelGGL(k_init_dt, dim3(1), dim3(1), 0, c->stream, c->sc);
     if (hipGetLastError() != hipSuccess) return MHD_ERR_HIP;
   }
@@ -975,10 +1009,11 @@ int mhd_step_batch(mhd_ctx* const* ctxs, const int* nsteps, int n, void* stream)
 
 int mhd_set_launch(mhd_ctx* c, int tile, int zchunk) {
   if (!c || zchunk < 0) return MHD_ERR_INVALID_ARG;
+  const bool shaped = tile != MHD_TILE_DEFAULT || zchunk != 0;
   if (tile == MHD_TILE_DEFAULT) tile = default_tile(c->p.precision);
   int tx, ty;
   if (!tile_dims(tile, &tx, &ty)) return MHD_ERR_INVALID_ARG;
-  return apply_shape(c, tile, zchunk);
+  return apply_shape(c, tile, zchunk, shaped);
 }
 
 int mhd_get_launch(const mhd_ctx* c, int* tile, int* zchunk) {
@@ -1011,13 +1046,15 @@ int mhd_tune(mhd_ctx* const* ctxs, int n, int reps, void* stream, mhd_tune_resul
       src[i] = {(unsigned char)u0, (unsigned char)(u0 == 0 ? 1 : 0), (unsigned char)u0};
     }
   const int def_tile = default_tile(ctxs[0]->p.precision);
+  // the default shape: what an untuned group gets, bricks where they are better
+  auto automatic = [&](int tile, int cap) { return tile == def_tile && cap == 0; };
   float best = 1e30f, def_ms = -1.0f;
   int best_tile = def_tile, best_cap = 0, tried = 0;
   // median first-stage time of the whole group in its current shapes (the
   // first launch warms up)
   auto time_group = [&](float* med) -> int {
     for (int r = 0; r <= reps; ++r) {
-      if (hipEventRecord(e0, st) != hipSuccess || launch_stage(ctxs, src, n, 0, 1.0, 0.0, nullptr, {}, st) != hipSuccess ||
+      if (hipEventRecord(e0, st) != hipSuccess || launch_stage(ctxs, src, n, 0, 1.0, 0.0, nullptr, nullptr, {}, st) != hipSuccess ||
           hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess)
         return MHD_ERR_HIP;
       float ms = 0.0f;
@@ -1045,7 +1082,7 @@ int mhd_tune(mhd_ctx* const* ctxs, int n, int reps, void* stream, mhd_tune_resul
           if (ctxs[i]->p.nz > caps[ci - 1] || caps[ci - 1] == 0) dup = false;
       }
       if (dup) continue;
-      for (int i = 0; i < n && rc == MHD_OK; ++i) rc = apply_shape(ctxs[i], tiles[ti], cap);
+      for (int i = 0; i < n && rc == MHD_OK; ++i) rc = apply_shape(ctxs[i], tiles[ti], cap, !automatic(tiles[ti], cap));
       if (rc != MHD_OK) break;
       float med = 0.0f;
       rc = time_group(&med);
@@ -1066,7 +1103,7 @@ int mhd_tune(mhd_ctx* const* ctxs, int n, int reps, void* stream, mhd_tune_resul
   if (rc == MHD_OK) {
     for (int i = 0; i < n && rc == MHD_OK; ++i) {
       cls_cap[i] = best_cap;
-      rc = apply_shape(ctxs[i], best_tile, best_cap);
+      rc = apply_shape(ctxs[i], best_tile, best_cap, !automatic(best_tile, best_cap));
     }
   }
   if (rc == MHD_OK && n > 1) {
@@ -1104,7 +1141,7 @@ int mhd_tune(mhd_ctx* const* ctxs, int n, int reps, void* stream, mhd_tune_resul
         // caps at or above nz all mean nz: try the first such once
         if (cap == keep || (cap > 0 && ci > 0 && caps[ci - 1] >= nzk)) continue;
         for (int i = 0; i < n && rc == MHD_OK; ++i)
-          if (ctxs[i]->p.nz == nzk) rc = apply_shape(ctxs[i], best_tile, cap);
+          if (ctxs[i]->p.nz == nzk) rc = apply_shape(ctxs[i], best_tile, cap, !automatic(best_tile, cap));
         float med = 0.0f;
         if (rc == MHD_OK) rc = time_group(&med);
         if (rc == MHD_OK && med < 0.99f * cur) {
@@ -1115,7 +1152,7 @@ int mhd_tune(mhd_ctx* const* ctxs, int n, int reps, void* stream, mhd_tune_resul
       for (int i = 0; i < n && rc == MHD_OK; ++i)
         if (ctxs[i]->p.nz == nzk) {
           cls_cap[i] = chosen;
-          rc = apply_shape(ctxs[i], best_tile, chosen);
+          rc = apply_shape(ctxs[i], best_tile, chosen, !automatic(best_tile, chosen));
         }
     }
     if (rc == MHD_OK) best = cur < best ? cur : best;
@@ -1129,16 +1166,17 @@ int mhd_tune(mhd_ctx* const* ctxs, int n, int reps, void* stream, mhd_tune_resul
       rc == MHD_OK)
     rc = MHD_ERR_HIP;
   if (rc == MHD_OK)
-    for (int i = 0; i < n && rc == MHD_OK; ++i) rc = apply_shape(ctxs[i], best_tile, cls_cap[i]);
+    for (int i = 0; i < n && rc == MHD_OK; ++i) rc = apply_shape(ctxs[i], best_tile, cls_cap[i], !automatic(best_tile, cls_cap[i]));
   // an automatic length depends on what is launched together: a group's is fixed as
   // it was timed, so that mhd_get_launch reports it
   if (rc == MHD_OK && n > 1) {
     for (int i0 = 0; i0 < n; i0 += kMaxBatch) {
       const int m = n - i0 < kMaxBatch ? n - i0 : kMaxBatch;
       short lz[kMaxBatch];
+      if (plan_brick(ctxs + i0, m) != BRICK_NONE) continue;  // nothing to fix
       plan_lz(ctxs + i0, m, lz);
       for (int i = 0; i < m && rc == MHD_OK; ++i)
-        if (cls_cap[i0 + i] == 0) rc = apply_shape(ctxs[i0 + i], best_tile, lz[i]);
+        if (cls_cap[i0 + i] == 0) rc = apply_shape(ctxs[i0 + i], best_tile, lz[i], true);
     }
   }
   free(cls_cap);

@@ -100,6 +100,13 @@ struct BoxDesc {
   long long ustride;
 };
 
+// Blocks of the small-box stage kernel (mhd_brick.inl): cells in x, y, z and threads.
+struct BrickShape {
+  int x, y, z, threads;
+};
+enum { BRICK_NONE = 0, BRICK_844 = 1, BRICK_442 = 2 };
+constexpr BrickShape kBrick[3] = {{0, 0, 0, 0}, {8, 4, 4, 1024}, {4, 4, 2, 512}};
+
 // One stage launch over up to kMaxBatch boxes: global block g belongs to the
 // box b with start[b] <= g < start[b + 1].  Box b applies S_dt to buffer
 // src[b] and writes buffer dst[b]; a combining stage writes
@@ -109,7 +116,7 @@ struct BatchArgs {
   int nbox, mode, total;
   int emf;  // corner-EMF scheme shared by the batch
   int ct;   // CT_FACE or CT_VECPOT, shared by the batch
-  int pad;
+  int brick;  // stage launch: BRICK_* shape of its blocks, or z-chunks of columns
   double w, w0;
   const BoxDesc* desc[kMaxBatch];
   int start[kMaxBatch + 1];
