@@ -137,7 +137,8 @@ class MHDBox:
         dt = C.c_double()
         v = _view(out)
         rc = self.lib.mhd_get_state(self.ctx, C.byref(v), C.byref(t), C.byref(dt))
-        torch.cuda.current_stream(self.device).wait_stream(self.stream)
+        if rc not in (L.MHD_OK, L.MHD_ERR_NONPHYSICAL):  # else it has waited for the stream
+            torch.cuda.current_stream(self.device).wait_stream(self.stream)
         if check:
             L.check(rc, "mhd_get_state")
         return out, t.value, dt.value, rc

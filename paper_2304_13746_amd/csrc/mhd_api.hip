@@ -91,6 +91,80 @@ __global__ void k_set(Scalars* s, double t, double dt_next, double cfl) {
   set_scalars(s, t, dt_next, cfl);
 }
 
+// ---- readback: the scalars that a synchronising call returns.
+//
+// A copy of 176 bytes to pageable memory stages through the runtime and waits on its own
+// (a scalars-only mhd_get_state took 21 us).  The last kernel of the call writes them to
+// a slot of pinned host memory instead, and the call's one synchronisation makes them
+// visible: 11 us.  The slots are one allocation of the process, made with the first
+// context; a call holds one while it waits, and falls back to the copy if all are taken.
+struct Readback {
+  static constexpr int kSlots = 64;
+  std::mutex mu;
+  Scalars* base = nullptr;
+  bool tried = false;
+  unsigned long long taken = 0;
+
+  void init() {
+    std::lock_guard<std::mutex> lock(mu);
+    if (tried) return;
+    tried = true;
+    void* p = nullptr;
+    if (hipHostMalloc(&p, sizeof(Scalars) * kSlots, hipHostMallocPortable | hipHostMallocCoherent) ==
+        hipSuccess)
+      base = static_cast<Scalars*>(p);
+    else
+      (void)hipGetLastError();
+  }
+  Scalars* take() {
+    std::lock_guard<std::mutex> lock(mu);
+    if (!base || taken == ~0ull) return nullptr;
+    const int i = __builtin_ctzll(~taken);
+    taken |= 1ull << i;
+    return base + i;
+  }
+  void give(Scalars* s) {
+    if (!s) return;
+    std::lock_guard<std::mutex> lock(mu);
+    taken &= ~(1ull << (s - base));
+  }
+};
+static_assert(Readback::kSlots == 64, "one bit per slot");
+Readback g_readback;
+
+// a slot for the length of a call
+struct Slot {
+  Scalars* s;
+  Slot() : s(g_readback.take()) {}
+  ~Slot() { g_readback.give(s); }
+  Slot(const Slot&) = delete;
+  Slot& operator=(const Slot&) = delete;
+};
+
+constexpr int kScalarWords = (int)(sizeof(Scalars) / 8);
+static_assert(sizeof(Scalars) % 8 == 0 && kScalarWords <= 64, "one lane per word");
+
+// Threads below kScalarWords copy the scalars to host memory.
+__device__ __forceinline__ void send_scalars(const Scalars* s, Scalars* host, int t) {
+  if (t >= kScalarWords) return;
+  const unsigned long long v = ld_agent(reinterpret_cast<const unsigned long long*>(s) + t);
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(host) + t, v, __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__global__ void k_send(const Scalars* s, Scalars* host) { send_scalars(s, host, threadIdx.x); }
+
+// Wait for the stream and read the scalars back: from the slot that a kernel of the
+// call has written, or by a copy.
+hipError_t read_scalars(const mhd_ctx* c, const Slot& slot, Scalars* h) {
+  if (!slot.s) {
+    hipError_t e = hipMemcpyAsync(h, c->sc, sizeof(Scalars), hipMemcpyDeviceToHost, c->stream);
+    return e == hipSuccess ? hipStreamSynchronize(c->stream) : e;
+  }
+  hipError_t e = hipStreamSynchronize(c->stream);
+  if (e == hipSuccess) memcpy(h, slot.s, sizeof(Scalars));
+  return e;
+}
+
 // ---- state copies: all fields of a state in one launch, with the scalars of a new
 // state.  For small boxes a copy is all launch: eight copies cost 8 to 10 us each on
 // the host and left the GPU idle between them, one pass of set_state, a cycle and
@@ -103,6 +177,8 @@ struct CopyArgs {
   long long bytes;  // of one field, a multiple of 4
   Scalars* sc;      // null: leave the scalars alone
   double t, dt_next, cfl;
+  const Scalars* from;  // with to: also read the scalars back
+  Scalars* to;
 };
 
 typedef unsigned Words4 __attribute__((ext_vector_type(4)));
@@ -131,6 +207,7 @@ __device__ __forceinline__ void copy_field(const void* src, void* dst, long long
 __global__ void __launch_bounds__(kCopyThreads) k_copy(CopyArgs a) {
   if (a.sc && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
     set_scalars(a.sc, a.t, a.dt_next, a.cfl);
+  if (a.to && blockIdx.x == 0 && blockIdx.y == 0) send_scalars(a.from, a.to, threadIdx.x);
   const void* src = a.src[blockIdx.y];
   void* dst = a.dst[blockIdx.y];
   const unsigned long long low = (uintptr_t)src | (uintptr_t)dst;
@@ -165,10 +242,11 @@ bool on_device(const void* ptr, size_t bytes, int dev, Extent& known) {
   return false;
 }
 
-// Copy nf fields (null sources are skipped) on st; with sc also set the scalars.
-// view: the caller's side of the copy, whose memory is looked at first.
+// Copy nf fields (null sources are skipped) on st; with sc also set the scalars, with to
+// read from's back.  view: the caller's side of the copy, whose memory is looked at first.
 hipError_t copy_fields(void* const* dst, void* const* src, int nf, size_t bytes, void* const* view,
-                       int dev, Scalars* sc, double t, double dt_next, double cfl, hipStream_t st) {
+                       int dev, Scalars* sc, double t, double dt_next, double cfl,
+                       const Scalars* from, Scalars* to, hipStream_t st) {
   CopyArgs a = {};
   int n = 0;
   bool direct = true;
@@ -185,6 +263,7 @@ hipError_t copy_fields(void* const* dst, void* const* src, int nf, size_t bytes,
       if (e != hipSuccess) return e;
     }
     if (sc) hipLaunchKernelGGL(k_set, dim3(1), dim3(1), 0, st, sc, t, dt_next, cfl);
+    if (to) hipLaunchKernelGGL(k_send, dim3(1), dim3(64), 0, st, from, to);
     return hipGetLastError();
   }
   a.bytes = (long long)bytes;
@@ -192,6 +271,8 @@ hipError_t copy_fields(void* const* dst, void* const* src, int nf, size_t bytes,
   a.t = t;
   a.dt_next = dt_next;
   a.cfl = cfl;
+  a.from = from;
+  a.to = to;
   // four 16-byte vectors a thread, up to 8 blocks per CU over the fields of a state
   const size_t want = (bytes + 64 * kCopyThreads - 1) / (64 * kCopyThreads);
   hipLaunchKernelGGL(k_copy, dim3((unsigned)(want < 256 ? want : 256), n), dim3(kCopyThreads), 0, st, a);
@@ -352,7 +433,7 @@ k_diag_partial(DiagFields fields, int nx, int ny, int nz, double idx, double idy
 // one block: thread t takes the partials of block t
 static_assert(kDiagBlocks <= kDiagThreads, "one thread per block of the first kernel");
 __global__ void __launch_bounds__(kDiagThreads)
-k_diag_final(const double* part, int nblocks, double dv, double ncell, Scalars* s) {
+k_diag_final(const double* part, int nblocks, double dv, double ncell, Scalars* s, Scalars* host) {
   DiagSums a = {};
   if ((int)threadIdx.x < nblocks) {
     const double* p = part + threadIdx.x;
@@ -368,11 +449,15 @@ k_diag_final(const double* part, int nblocks, double dv, double ncell, Scalars* 
     st_agent(&s->diag[8], a.dmax);
     st_agent(&s->diag[9], sqrt((a.acc[8].s + a.acc[8].c) / ncell));
   }
+  __threadfence();  // thread 0's results before the loads below
+  __syncthreads();
+  if (host) send_scalars(s, host, threadIdx.x);
 }
 
 // Diagnostics of c's state with the per-block partial sums in part (the
 // context's workspace, or the static scratch of the allocation-free variant).
 int diagnostics_into(mhd_ctx* c, double* part, mhd_diag* out) {
+  Slot slot;
   DiagFields f;
   for (int q = 0; q < 8; ++q) f.f[q] = c->buf[c->cur][q];
   auto fn = c->p.precision == MHD_FP32 ? k_diag_partial<float> : k_diag_partial<double>;
@@ -380,12 +465,10 @@ int diagnostics_into(mhd_ctx* c, double* part, mhd_diag* out) {
                      c->p.ny, c->p.nz, c->idl[0], c->idl[1], c->idl[2], part);
   if (hipGetLastError() != hipSuccess) return MHD_ERR_HIP;
   hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(kDiagThreads), 0, c->stream, part, c->diag_blocks, c->dv,
-                     (double)c->ncell, c->sc);
+                     (double)c->ncell, c->sc, slot.s);
   if (hipGetLastError() != hipSuccess) return MHD_ERR_HIP;
   Scalars h;
-  hipError_t e = hipMemcpyAsync(&h, c->sc, sizeof(Scalars), hipMemcpyDeviceToHost, c->stream);
-  if (e != hipSuccess) return MHD_ERR_HIP;
-  if (hipStreamSynchronize(c->stream) != hipSuccess) return MHD_ERR_HIP;
+  if (read_scalars(c, slot, &h) != hipSuccess) return MHD_ERR_HIP;
   out->mass = h.diag[0];
   for (int d = 0; d < 3; ++d) out->mom[d] = h.diag[1 + d];
   out->energy = h.diag[4];
@@ -855,6 +938,7 @@ int mhd_create(const mhd_params* p, mhd_ctx** out) {
 
   mhd_ctx* c = (mhd_ctx*)calloc(1, sizeof(mhd_ctx));
   if (!c) return MHD_ERR_INVALID_ARG;
+  g_readback.init();
   c->p = *p;
   c->stream = (hipStream_t)p->stream;
   if (hipGetDevice(&c->device) != hipSuccess) {
@@ -918,7 +1002,7 @@ int mhd_set_state(mhd_ctx* c, const mhd_state_view* v, double t, double dt_next)
   c->stages_valid = 0;
   if (vp) src[5] = src[6] = src[7] = nullptr;
   if (copy_fields(c->buf[0], src, c->nfield, bytes, src, c->device, c->sc, t, dt_next, c->p.cfl,
-                  c->stream) != hipSuccess)
+                  nullptr, nullptr, c->stream) != hipSuccess)
     return MHD_ERR_HIP;
   if (vp) {
     const Roles r0 = {0, 0, 0};
@@ -942,6 +1026,7 @@ int mhd_step(mhd_ctx* c, int nsteps, double t_stop) {
 int mhd_get_state(mhd_ctx* c, const mhd_state_view* v, double* t, double* dt_next) {
   Range range("mhd_get_state");
   if (!c) return MHD_ERR_INVALID_ARG;
+  Slot slot;
   if (v) {
     void* dst[11];
     fields_of(v, dst);
@@ -951,14 +1036,14 @@ int mhd_get_state(mhd_ctx* c, const mhd_state_view* v, double* t, double* dt_nex
     // the potential is copied out when the view asks for it
     const int nf = c->nfield == 11 && dst[8] && dst[9] && dst[10] ? 11 : 8;
     if (copy_fields(dst, c->buf[c->cur], nf, bytes, dst, c->device, nullptr, 0.0, 0.0, 0.0,
-                    c->stream) != hipSuccess)
+                    c->sc, slot.s, c->stream) != hipSuccess)
       return MHD_ERR_HIP;
+  } else if (slot.s) {
+    hipLaunchKernelGGL(k_send, dim3(1), dim3(64), 0, c->stream, c->sc, slot.s);
+    if (hipGetLastError() != hipSuccess) return MHD_ERR_HIP;
   }
   Scalars h;
-  hipError_t e = hipMemcpyAsync(&h, c->sc, sizeof(Scalars), hipMemcpyDeviceToHost, c->stream);
-  if (e != hipSuccess) return MHD_ERR_HIP;
-  e = hipStreamSynchronize(c->stream);
-  if (e != hipSuccess) return MHD_ERR_HIP;
+  if (read_scalars(c, slot, &h) != hipSuccess) return MHD_ERR_HIP;
   if (t) *t = h.t;
   if (dt_next) *dt_next = h.dt_next;
   return h.status ? MHD_ERR_NONPHYSICAL : MHD_OK;
@@ -975,8 +1060,8 @@ int mhd_get_stage_output(mhd_ctx* c, int stage, const mhd_state_view* v) {
     if (!dst[f]) return MHD_ERR_INVALID_ARG;
   const int nf = c->nfield == 11 && dst[8] && dst[9] && dst[10] ? 11 : 8;
   const size_t bytes = (size_t)c->ncell * c->elem;
-  if (copy_fields(dst, c->buf[stage], nf, bytes, dst, c->device, nullptr, 0.0, 0.0, 0.0, c->stream) !=
-      hipSuccess)
+  if (copy_fields(dst, c->buf[stage], nf, bytes, dst, c->device, nullptr, 0.0, 0.0, 0.0, nullptr,
+                  nullptr, c->stream) != hipSuccess)
     return MHD_ERR_HIP;
   return hipStreamSynchronize(c->stream) == hipSuccess ? MHD_OK : MHD_ERR_HIP;
 }
