@@ -31,9 +31,8 @@ struct mhd_ctx {
   BoxDesc* desc;     // device copy of this box's descriptor
   double* diag_part; // per-block diagnostic partials
   int tile, zchunk;  // launch shape as requested (zchunk 0 = automatic)
-  bool shaped;       // tile or zchunk was requested: march, whatever the size
-  int lz;            // z-planes per work-group: as requested, or when stepped alone
-  int cols;          // x-y tiles of the box
+  bool shaped;       // tile or zchunk was requested: that shape, whatever the size
+  int lone_tile, lz; // tile and z-planes per work-group: as requested, or when stepped alone
   int diag_blocks;
   int stages_valid;  // intermediate buffers hold the last cycle's stage results
 };
@@ -598,46 +597,69 @@ int plan_brick(mhd_ctx* const* c, int n) {
   return small <= kCus ? BRICK_442 : big <= kCus ? BRICK_844 : BRICK_NONE;
 }
 
-// The lz of n contexts launched together (n <= kMaxBatch): the requested one, or one
-// common length for all the automatic ones.
-void plan_lz(mhd_ctx* const* c, int n, short* lz) {
+// The tile and the lz of n contexts launched together (n <= kMaxBatch): the requested
+// ones, or one common length for all that leave it open, and if none asks for anything
+// the tile with the smaller launch_cost.  24x8 and 18x11 both fill a 256-thread block; at
+// equal counts 18x11 took 2 to 5 % longer (256^3), so it has to save that: 101x75 is 50
+// columns of 24x8 and 42 of 18x11.
+constexpr double kTile1811 = 1.04;
+
+void plan_march(mhd_ctx* const* c, int n, int* tile, short* lz) {
   int zmax = 0;
+  bool shaped = false;
   for (int i = 0; i < n; ++i) {
     lz[i] = (short)c[i]->lz;
+    shaped = shaped || c[i]->shaped;
     if (c[i]->zchunk == 0 && c[i]->p.nz > zmax) zmax = c[i]->p.nz;
   }
+  *tile = c[0]->tile;
   if (zmax == 0) return;
   double best = 0.0;
   int pick = 0;
-  // every length for one box (planned once, when it takes its launch shape); for a
-  // group, planned as boxes leave it, every length up to 16 and then steps of an eighth
-  for (int z = 1; z <= zmax; z += n == 1 || z < 16 ? 1 : z / 8) {
-    long long blocks = 0;
-    for (int i = 0; i < n; ++i)
-      blocks += (long long)c[i]->cols * chunks(c[i]->p.nz, c[i]->zchunk ? c[i]->lz : z);
-    double t = launch_cost(&c[0]->p, blocks, z);
-    // a large box: whole z-slabs for each of the 8 XCDs, or halo planes miss its L2
-    if (n == 1 && blocks >= 4 * kCus && chunks(zmax, z) % 8 != 0) t *= kSlabs;
-    if (pick == 0 || t < best) {
-      best = t;
-      pick = z;
+  for (int second = 0; second < (shaped ? 1 : 2); ++second) {
+    const int tl = second ? (int)TILE_18x11 : c[0]->tile;
+    // every length for one box (planned once, when it takes its launch shape); for a
+    // group, planned as boxes leave it, every length up to 16 and then steps of an eighth
+    for (int z = 1; z <= zmax; z += n == 1 || z < 16 ? 1 : z / 8) {
+      long long blocks = 0;
+      for (int i = 0; i < n; ++i)
+        blocks += columns(&c[i]->p, tl) * chunks(c[i]->p.nz, c[i]->zchunk ? c[i]->lz : z);
+      double t = launch_cost(&c[0]->p, blocks, z) * (second ? kTile1811 : 1.0);
+      // a large box: whole z-slabs for each of the 8 XCDs, or halo planes miss its L2
+      if (n == 1 && blocks >= 4 * kCus && chunks(zmax, z) % 8 != 0) t *= kSlabs;
+      if (pick == 0 || t < best) {
+        best = t;
+        pick = z;
+        *tile = tl;
+      }
     }
   }
   for (int i = 0; i < n; ++i)
     if (c[i]->zchunk == 0) lz[i] = (short)(pick < c[i]->p.nz ? pick : c[i]->p.nz);
 }
 
+// How the stages of up to kMaxBatch contexts are launched.
+struct Plan {
+  int brick, tile;
+  short lz[kMaxBatch];
+};
+Plan plan_launch(mhd_ctx* const* c, int n) {
+  Plan p;
+  p.brick = plan_brick(c, n);
+  plan_march(c, n, &p.tile, p.lz);
+  return p;
+}
+
 // One stage launch over n contexts sharing precision, solver and tile, with
-// weights (w, w0) for a combining stage, lz[i] planes per block of context i and
-// brick[j] for the j-th chunk of the batch (null: planned here).  Batches beyond
-// kMaxBatch go out in chunks.
+// weights (w, w0) for a combining stage and one plan per kMaxBatch contexts (null:
+// planned here).  Batches beyond kMaxBatch go out in chunks.
 struct Control {
   int par, first, last;   // as in BatchArgs
   const double* t_stop;   // per context
 };
 
 hipError_t launch_stage(mhd_ctx* const* c, const Roles* r, int n, int mode, double w, double w0,
-                        const short* lz, const unsigned char* brick, const Control& ctl, hipStream_t st) {
+                        const Plan* plans, const Control& ctl, hipStream_t st) {
   for (int i0 = 0; i0 < n; i0 += kMaxBatch) {
     const int m = n - i0 < kMaxBatch ? n - i0 : kMaxBatch;
     BatchArgs ba = {};
@@ -651,13 +673,9 @@ hipError_t launch_stage(mhd_ctx* const* c, const Roles* r, int n, int mode, doub
     ba.first = ctl.first;
     ba.last = ctl.last;
     if (ctl.t_stop) memcpy(ba.t_stop, ctl.t_stop + i0, sizeof(double) * m);
-    if (lz) {
-      memcpy(ba.lz, lz + i0, sizeof(short) * m);
-      ba.brick = brick[i0 / kMaxBatch];
-    } else {
-      plan_lz(c + i0, m, ba.lz);
-      ba.brick = mode != 2 ? plan_brick(c + i0, m) : BRICK_NONE;  // measuring marches
-    }
+    const Plan plan = plans ? plans[i0 / kMaxBatch] : plan_launch(c + i0, m);
+    memcpy(ba.lz, plan.lz, sizeof(short) * m);
+    ba.brick = mode != 2 ? plan.brick : BRICK_NONE;  // measuring marches
     int g = 0;
     for (int i = 0; i < m; ++i) {
       const mhd_ctx* ci = c[i0 + i];
@@ -667,12 +685,12 @@ hipError_t launch_stage(mhd_ctx* const* c, const Roles* r, int n, int mode, doub
       ba.dst[i] = r[i0 + i].dst;
       ba.base[i] = r[i0 + i].base;
       g += ba.brick != BRICK_NONE ? (int)bricks(&ci->p, kBrick[ba.brick])
-                                  : (int)ci->cols * chunks(ci->p.nz, ba.lz[i]);
+                                  : (int)columns(&ci->p, plan.tile) * chunks(ci->p.nz, ba.lz[i]);
     }
     ba.start[m] = g;
     ba.total = g;
     const mhd_ctx* c0 = c[i0];
-    hipError_t e = stage_kernel(&c0->p, ba, c0->tile, st, false);
+    hipError_t e = stage_kernel(&c0->p, ba, plan.tile, st, false);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -771,8 +789,7 @@ int step_group(mhd_ctx* const* c, const int* nsteps, int n, const double* t_stop
   static thread_local mhd_ctx* act[4096];
   static thread_local Roles roles[4096];
   static thread_local double ts[4096];
-  static thread_local short lz[4096];
-  static thread_local unsigned char brick[4096 / kMaxBatch];
+  static thread_local Plan plans[4096 / kMaxBatch];
   int m = 0;
   const int integ = c[0]->p.integrator;
   const bool vp = c[0]->p.ct == MHD_CT_VECPOT;
@@ -784,11 +801,8 @@ int step_group(mhd_ctx* const* c, const int* nsteps, int n, const double* t_stop
     for (int i = 0; i < n; ++i)
       if (nsteps[i] > cyc) { act[m] = c[i]; ts[m] = t_stop ? t_stop[i] : 0.0; ++m; }
     if (cyc == 0 || m != was)  // boxes only ever leave
-      for (int i = 0; i < m; i += kMaxBatch) {
-        const int k = m - i < kMaxBatch ? m - i : kMaxBatch;
-        plan_lz(act + i, k, lz + i);
-        brick[i / kMaxBatch] = (unsigned char)plan_brick(act + i, k);
-      }
+      for (int i = 0; i < m; i += kMaxBatch)
+        plans[i / kMaxBatch] = plan_launch(act + i, m - i < kMaxBatch ? m - i : kMaxBatch);
     // stage 1: U_1 = S_dt(U_0), measuring the next dt (eq. cfl)
     for (int i = 0; i < m; ++i) {
       const int u0 = act[i]->cur;
@@ -800,7 +814,7 @@ int step_group(mhd_ctx* const* c, const int* nsteps, int n, const double* t_stop
     const int par = cyc & 1;
     auto stage = [&](int mode, double w, double w0, bool last) -> bool {
       const Control ctl = {par, cyc == 0 && mode == 0, last, ts};
-      if (launch_stage(act, roles, m, mode, w, w0, lz, brick, ctl, st) != hipSuccess) return false;
+      if (launch_stage(act, roles, m, mode, w, w0, plans, ctl, st) != hipSuccess) return false;
       if (uct && launch_uct(act, roles, m, mode, w, w0, par, !vp, st) != hipSuccess) return false;
       return !vp || launch_vpot(act, roles, m, mode, w, w0, par, true, st) == hipSuccess;
     };
@@ -836,6 +850,7 @@ int apply_shape(mhd_ctx* c, int tile, int zchunk, bool shaped) {
   none.emf = p->emf;
   none.ct = p->ct;
   hipError_t e = stage_kernel(p, none, tile, nullptr, true);
+  if (e == hipSuccess && !shaped) e = stage_kernel(p, none, TILE_18x11, nullptr, true);
   if (e != hipSuccess) return MHD_ERR_HIP;
   BoxDesc d = {};
   for (int b = 0; b < c->nbuf; ++b)
@@ -847,8 +862,6 @@ int apply_shape(mhd_ctx* c, int tile, int zchunk, bool shaped) {
   d.nx = p->nx;
   d.ny = p->ny;
   d.nz = p->nz;
-  d.ntx = (p->nx + tx - 1) / tx;
-  d.nty = (p->ny + ty - 1) / ty;
   for (int k = 0; k < 3; ++k) d.idl[k] = c->idl[k];
   d.gamma = p->gamma;
   d.sc = c->sc;
@@ -860,11 +873,11 @@ int apply_shape(mhd_ctx* c, int tile, int zchunk, bool shaped) {
   c->tile = tile;
   c->zchunk = zchunk;
   c->shaped = shaped;
-  c->cols = (int)columns(p, tile);
+  c->lone_tile = tile;
   c->lz = zchunk < p->nz ? zchunk : p->nz;
   if (zchunk == 0) {
     short lz;
-    plan_lz(&c, 1, &lz);
+    plan_march(&c, 1, &c->lone_tile, &lz);
     c->lz = lz;
   }
   return MHD_OK;
@@ -1011,7 +1024,7 @@ int mhd_set_state(mhd_ctx* c, const mhd_state_view* v, double t, double dt_next)
   if (!(dt_next > 0.0)) {
     // eq. (cfl) on the initial state: the stage kernel in measuring mode
     const Roles r0 = {0, 1, 0};
-    if (launch_stage(&c, &r0, 1, 2, 1.0, 0.0, nullptr, nullptr, {}, c->stream) != hipSuccess) return MHD_ERR_HIP;
+    if (launch_stage(&c, &r0, 1, 2, 1.0, 0.0, nullptr, {}, c->stream) != hipSuccess) return MHD_ERR_HIP;
     hipLaunchKernelGGL(k_init_dt, dim3(1), dim3(1), 0, c->stream, c->sc);
     if (hipGetLastError() != hipSuccess) return MHD_ERR_HIP;
   }
@@ -1103,7 +1116,7 @@ int mhd_set_launch(mhd_ctx* c, int tile, int zchunk) {
 
 int mhd_get_launch(const mhd_ctx* c, int* tile, int* zchunk) {
   if (!c) return MHD_ERR_INVALID_ARG;
-  if (tile) *tile = c->tile;
+  if (tile) *tile = c->lone_tile;
   if (zchunk) *zchunk = c->lz;
   return MHD_OK;
 }
@@ -1139,7 +1152,7 @@ int mhd_tune(mhd_ctx* const* ctxs, int n, int reps, void* stream, mhd_tune_resul
   // first launch warms up)
   auto time_group = [&](float* med) -> int {
     for (int r = 0; r <= reps; ++r) {
-      if (hipEventRecord(e0, st) != hipSuccess || launch_stage(ctxs, src, n, 0, 1.0, 0.0, nullptr, nullptr, {}, st) != hipSuccess ||
+      if (hipEventRecord(e0, st) != hipSuccess || launch_stage(ctxs, src, n, 0, 1.0, 0.0, nullptr, {}, st) != hipSuccess ||
           hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess)
         return MHD_ERR_HIP;
       float ms = 0.0f;
@@ -1257,9 +1270,12 @@ int mhd_tune(mhd_ctx* const* ctxs, int n, int reps, void* stream, mhd_tune_resul
   if (rc == MHD_OK && n > 1) {
     for (int i0 = 0; i0 < n; i0 += kMaxBatch) {
       const int m = n - i0 < kMaxBatch ? n - i0 : kMaxBatch;
-      short lz[kMaxBatch];
       if (plan_brick(ctxs + i0, m) != BRICK_NONE) continue;  // nothing to fix
-      plan_lz(ctxs + i0, m, lz);
+      for (int i = 0; i < m && rc == MHD_OK; ++i)
+        rc = apply_shape(ctxs[i0 + i], best_tile, cls_cap[i0 + i], true);
+      short lz[kMaxBatch];
+      int tile;
+      plan_march(ctxs + i0, m, &tile, lz);
       for (int i = 0; i < m && rc == MHD_OK; ++i)
         if (cls_cap[i0 + i] == 0) rc = apply_shape(ctxs[i0 + i], best_tile, lz[i], true);
     }
@@ -1270,7 +1286,7 @@ int mhd_tune(mhd_ctx* const* ctxs, int n, int reps, void* stream, mhd_tune_resul
   free(src);
   free(times);
   if (rc == MHD_OK && out) {
-    out->tile = best_tile;
+    out->tile = n == 1 ? ctxs[0]->lone_tile : best_tile;
     out->zchunk_cap = best_cap;
     out->best_ms = best;
     out->default_ms = def_ms;

@@ -75,8 +75,8 @@ __device__ __forceinline__ void end_cycle(Scalars* s, int par, double t_stop) {
 enum { TILE_16x16 = 1, TILE_24x8 = 2, TILE_18x11 = 3 };
 
 // One box as the stage kernel sees it; each context keeps its descriptor in its
-// own workspace (rewritten only when its launch shape changes).  How many z-planes a
-// block marches is a property of the launch, not of the box: see BatchArgs::lz.
+// own workspace (rewritten only when its launch shape changes).  The tile of a
+// block and the z-planes that it marches are properties of the launch, not of the box.
 constexpr int kMaxBuf = 3;  // state buffers: U_0 and up to two stage results
 // fields of a buffer: rho mx my mz en bx by bz, and with the vector-potential
 // form of constrained transport the edge potential ax ay az
@@ -85,7 +85,6 @@ enum { CT_FACE = 0, CT_VECPOT = 1 };
 struct BoxDesc {
   void* buf[kMaxBuf][kFields];
   int nx, ny, nz;
-  int ntx, nty;           // tiles of the context's tile shape
   int ct;                 // CT_FACE or CT_VECPOT
   double idl[3];          // 1 / dl_d
   double gamma;

@@ -517,7 +517,7 @@ stage_kernel(BatchArgs ba) {
     a.w = (R)ba.w;
     a.w0 = (R)ba.w0;
     a.nx = d->nx; a.ny = d->ny; a.nz = d->nz;
-    a.ntx = d->ntx; a.nty = d->nty; a.lz = ba.lz[box];
+    a.ntx = (a.nx + TX - 1) / TX; a.nty = (a.ny + TY - 1) / TY; a.lz = ba.lz[box];
     for (int k = 0; k < 3; ++k) a.idl[k] = (R)d->idl[k];
     a.gamma = (R)d->gamma;
     a.gm1 = (R)(d->gamma - 1.0);

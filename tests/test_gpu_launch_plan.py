@@ -57,3 +57,22 @@ def test_group_with_requested_and_automatic_lengths(tmp_path):
     assert {str(d[2]) for d in dims} == set(choice["zchunk_by_nz"])
     for d, box in zip(dims, boxes):
         assert 1 <= box.get_launch()[1] <= d[2]
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_automatic_tile(precision):
+    """A box that 18x11 columns cover better takes them, with the bits of 24x8."""
+    need_gpu()
+    from paper_2304_13746_amd import _lib as L
+    dims = (54, 55, 40)
+    s = I.turbulence(dims, seed=31, kpeak=2.0, mach=0.7, b0=(0.2, -0.1, 0.3))
+    l = s.pop("_l")
+    out = []
+    for tile in (0, L.TILE_24x8):
+        box = gpu_box(dims, l, precision=precision, tile=tile)
+        assert box.get_launch()[0] == (L.TILE_18x11 if tile == 0 else tile)
+        box.set_state(s)
+        box.step(3)
+        out.append(box.get_state_numpy()[:3])
+        box.close()
+    assert bit_equal(out[0][0], out[1][0]) and out[0][1:] == out[1][1:]
