@@ -108,7 +108,8 @@ typedef struct {
   void* workspace;        /* device pointer, 256-byte aligned, BORROWED */
   size_t workspace_bytes; /* >= mhd_workspace_bytes(this) */
   void* stream;           /* hipStream_t to enqueue on (NULL: default stream) */
-  int tile;               /* MHD_TILE_*, 0 = default (24x8) */
+  int tile;               /* MHD_TILE_*, 0 = default: with zchunk 0 chosen for each launch,
+                             else 24x8 */
   int zchunk;             /* z-planes per thread block, 0 = automatic */
   int recon;              /* mhd_recon */
   int ct;                 /* mhd_ct */
@@ -193,9 +194,9 @@ int mhd_get_diagnostics_noalloc(mhd_ctx* ctx, mhd_diag* out);
 /* Advance n (0 <= n <= 4096) contexts by nsteps[i] >= 0 cycles each on one
  * stream (NULL: the stream of ctxs[0]).  Each stage of a cycle is one launch
  * whose blocks cover the tiles of every box still stepping (up to 64 boxes per
- * launch), followed by one cycle-control launch for all of them; each box keeps
- * its own step size, time and status latch, and gives the same bits as
- * mhd_step on it alone.  All contexts must share device, precision, solver,
+ * launch) and which also begins and ends the cycle (MHD_EULER: one cycle-control
+ * launch more); each box keeps its own step size, time and status latch, and gives
+ * the same bits as mhd_step on it alone.  All contexts must share device, precision, solver,
  * integrator, EMF scheme, reconstruction and tile shape (else MHD_ERR_UNSUPPORTED); a null entry or a
  * negative count is MHD_ERR_INVALID_ARG.  The contexts' own streams are not
  * synchronised with: order them against the batch stream first.  Asynchronous,
@@ -208,9 +209,13 @@ int mhd_step_batch(mhd_ctx* const* ctxs, const int* nsteps, int n, void* stream)
  * mhd_set_launch synchronises the context's stream; it must not be called while
  * a captured graph that contains this context is still to be replayed (the
  * graph keeps the launch grid it was captured with).  An automatic length is
- * chosen for each launch from everything that it covers: mhd_get_launch returns
- * the tile and the z-planes per work-group in effect when the context is stepped
- * alone (either pointer may be NULL). */
+ * chosen for each launch from everything that it covers, and where no context of
+ * it asks for a tile or a length, so is the tile (24x8 or 18x11).  mhd_get_launch
+ * returns the tile and the z-planes per work-group in effect when the context is
+ * stepped alone (either pointer may be NULL).  FP64 launches of the default scheme
+ * (PLM, E^c, face fields) for which nothing is asked, small enough that a GPU has a
+ * compute unit for every brick of 8x4x4 cells, run as bricks instead of columns;
+ * mhd_get_launch still returns the columns' shape, and asking for it gives columns. */
 int mhd_set_launch(mhd_ctx* ctx, int tile, int zchunk);
 int mhd_get_launch(const mhd_ctx* ctx, int* tile, int* zchunk);
 

@@ -167,8 +167,9 @@ hipError_t read_scalars(const mhd_ctx* c, const Slot& slot, Scalars* h) {
 // ---- state copies: all fields of a state in one launch, with the scalars of a new
 // state.  For small boxes a copy is all launch: eight copies cost 8 to 10 us each on
 // the host and left the GPU idle between them, one pass of set_state, a cycle and
-// get_state on a 16^3 box 193 us; one launch each way takes it to 145 us.  Large ones
-// run at the card's copy rate either way.
+// get_state on a 16^3 box 193 us; one launch each way takes it to 145 us (83 with the
+// scalars through pinned memory and the stages as bricks).  Large ones run at the card's
+// copy rate either way.
 constexpr int kCopyThreads = 256;
 struct CopyArgs {
   const void* src[kFields];
@@ -241,6 +242,19 @@ bool on_device(const void* ptr, size_t bytes, int dev, Extent& known) {
   return false;
 }
 
+// Whether copying fields in any order gives what one after another gives: no destination
+// overlaps another field's source or destination.
+bool any_order(const CopyArgs& a, int n, size_t bytes) {
+  auto apart = [&](const void* p, const void* q) {
+    const uintptr_t x = (uintptr_t)p, y = (uintptr_t)q;
+    return x < y ? y - x >= bytes : x - y >= bytes;
+  };
+  for (int f = 0; f < n; ++f)
+    for (int g = 0; g < n; ++g)
+      if (f != g && (!apart(a.dst[f], a.src[g]) || !apart(a.dst[f], a.dst[g]))) return false;
+  return true;
+}
+
 // Copy nf fields (null sources are skipped) on st; with sc also set the scalars, with to
 // read from's back.  view: the caller's side of the copy, whose memory is looked at first.
 hipError_t copy_fields(void* const* dst, void* const* src, int nf, size_t bytes, void* const* view,
@@ -256,7 +270,7 @@ hipError_t copy_fields(void* const* dst, void* const* src, int nf, size_t bytes,
     a.src[n] = src[f];
     a.dst[n++] = dst[f];
   }
-  if (!direct) {
+  if (!direct || !any_order(a, n, bytes)) {
     for (int f = 0; f < n; ++f) {
       hipError_t e = hipMemcpyAsync(a.dst[f], a.src[f], bytes, hipMemcpyDeviceToDevice, st);
       if (e != hipSuccess) return e;
@@ -315,7 +329,7 @@ __global__ void k_end(CtlArgs a) {
 // advanced by additions (64-bit divisions per cell took longer than the loads), then
 // waves and blocks combine their (sum, compensation) pairs as trees.  With one thread
 // combining a block's 256 pairs and one thread the 512 blocks', a call took 1.85 ms;
-// now the two kernels take 0.19 ms (5.7 TB/s read) and 11 us, a call 0.22 ms.
+// now the two kernels take 0.19 ms (5.7 TB/s read) and 11 us, a call 0.21 ms.
 constexpr int kDiagThreads = 512;
 constexpr int kDiagWaves = kDiagThreads / 64;
 
@@ -542,11 +556,12 @@ struct Roles {
 // blocks put ceil(N / 256) on a CU, so a launch takes
 //   (lz + kHead) (full rounds of resident blocks + the last, partly filled round),
 // and the rule takes the lz with the smallest, a box of its own with a preference for
-// chunk counts that the XCDs divide.  Measured per RK2 cycle (FP64, in us): 32^3 353
-// with 16 planes, the floor that an earlier rule had, and 68 with 1; 101x75x52 365 with
-// 16 and 242 with 6; 256^3 5.62, 5.64, 5.79, 5.62, 5.46, 5.64, 5.91 and 5.83 ms with 16,
-// 20, 22, 26, 32, 37, 43 and 64, and the rule takes 32.  On five boxes between 128^3 and
-// 256^3 in both precisions its choice is within 3.5 % of the best of ten lengths.
+// chunk counts that the XCDs divide.  Measured per RK2 cycle (FP64, in us, before the
+// quotients without scaling took 15 % off all of them): 32^3 353 with 16 planes, the floor
+// that an earlier rule had, and 68 with 1; 101x75x52 365 with 16 and 242 with 6; 256^3
+// 5.62, 5.64, 5.79, 5.62, 5.46, 5.64, 5.91 and 5.83 ms with 16, 20, 22, 26, 32, 37, 43 and
+// 64, and the rule takes 32.  On five boxes between 128^3 and 256^3 in both precisions its
+// choice is within 3.5 % of the best of ten lengths.
 constexpr int kCus = 256;
 constexpr double kHead = 2.2;
 constexpr double kSlabs = 1.06;
@@ -1148,11 +1163,14 @@ int mhd_tune(mhd_ctx* const* ctxs, int n, int reps, void* stream, mhd_tune_resul
   auto automatic = [&](int tile, int cap) { return tile == def_tile && cap == 0; };
   float best = 1e30f, def_ms = -1.0f;
   int best_tile = def_tile, best_cap = 0, tried = 0;
-  // median first-stage time of the whole group in its current shapes (the
-  // first launch warms up)
+  // median first-stage time of the whole group in its current shapes, planned before it
+  // starts, as mhd_step_batch does (the first launch warms up)
+  static thread_local Plan plans[4096 / kMaxBatch];
   auto time_group = [&](float* med) -> int {
+    for (int i = 0; i < n; i += kMaxBatch)
+      plans[i / kMaxBatch] = plan_launch(ctxs + i, n - i < kMaxBatch ? n - i : kMaxBatch);
     for (int r = 0; r <= reps; ++r) {
-      if (hipEventRecord(e0, st) != hipSuccess || launch_stage(ctxs, src, n, 0, 1.0, 0.0, nullptr, {}, st) != hipSuccess ||
+      if (hipEventRecord(e0, st) != hipSuccess || launch_stage(ctxs, src, n, 0, 1.0, 0.0, plans, {}, st) != hipSuccess ||
           hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess)
         return MHD_ERR_HIP;
       float ms = 0.0f;

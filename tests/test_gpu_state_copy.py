@@ -58,3 +58,26 @@ def test_pinned_host_arrays():
     for f in FIELDS:
         assert torch.equal(src[f], dst[f])
     box.close()
+
+
+def test_arrays_that_overlap():
+    """Fields that go to one array, in part or as a whole: the last one stands, as
+    with one copy after another."""
+    torch = need_gpu()
+    from paper_2304_13746_amd import _lib as L
+    from paper_2304_13746_amd.box import _view
+    dims, n = (64, 33, 31), 64 * 33 * 31
+    box = gpu_box(dims)
+    src = {f: torch.rand(n, dtype=torch.float64, device="cuda") + 1.0 for f in FIELDS}
+    big = torch.zeros(n + 100, dtype=torch.float64, device="cuda")
+    dst = {f: torch.zeros(n, dtype=torch.float64, device="cuda") for f in FIELDS}
+    dst["mx"] = dst["my"] = big[:n]
+    dst["en"] = big[100:]
+    torch.cuda.synchronize()
+    L.check(box.lib.mhd_set_state(box.ctx, C.byref(_view(src)), 0.0, 1e-3), "set")
+    L.check(box.lib.mhd_get_state(box.ctx, C.byref(_view(dst)), None, None), "get")
+    assert torch.equal(big[:100], src["my"][:100])
+    for f in FIELDS:
+        if f not in ("mx", "my"):
+            assert torch.equal(src[f], dst[f]), f
+    box.close()
