@@ -60,6 +60,14 @@ __device__ __forceinline__ void gst(R* p, long long o, R v) {
   ((__attribute__((address_space(1))) R*)p)[o] = v;
 }
 
+// w u + w0 u0 of a combining stage.  FP32 is built with contraction: which of the two
+// products it leaves rounded is said here, whatever code surrounds it.
+template <typename R>
+__device__ __forceinline__ R weigh(R w, R u, R w0, R u0) {
+  if constexpr (sizeof(R) == 4) return __builtin_fmaf(w, u, w0 * u0);
+  return w * u + w0 * u0;
+}
+
 __device__ __forceinline__ int wrapi(int i, int n) {
   i %= n;
   return i < 0 ? i + n : i;
@@ -974,8 +982,9 @@ stage_kernel(BatchArgs ba) {
     // with them)
 
     // FP32: what the update of plane m-1 reads from memory, ahead of the corner EMFs whose
-    // branches the compiler does not move loads across
-    constexpr bool PU = sizeof(R) == 4 && MODE != MODE_MEASURE;
+    // branches the compiler does not move loads across (256^3, a cycle 2.07 -> 2.00 ms; PPM
+    // has no registers for it: an RK3 cycle 9.0 ms with it, 8.7 without)
+    constexpr bool PU = sizeof(R) == 4 && !PPM && MODE != MODE_MEASURE;
     constexpr bool FB = !NE && CT == CT_FACE;  // the face field is updated here
     const long long ou = (long long)wrapi(m - 1, a.nz) * plane + col;
     R u0[PU && MODE == MODE_COMBINE ? 5 : 1], bs[PU && FB ? 2 : 1], b0[PU && FB && MODE == MODE_COMBINE ? 3 : 1];
@@ -1056,7 +1065,7 @@ stage_kernel(BatchArgs ba) {
         for (int q = 0; q < 5; ++q) un[q] = pt_(q) - tau_z * (fz.cons[q] - fzp(q));
         if constexpr (MODE == MODE_COMBINE) {
 #pragma unroll
-          for (int q = 0; q < 5; ++q) un[q] = a.w * un[q] + a.w0 * (PU ? u0[PU ? q : 0] : gld<R>(a.dst[q], o + a.boff));
+          for (int q = 0; q < 5; ++q) un[q] = weigh(a.w, un[q], a.w0, PU ? u0[PU ? q : 0] : gld<R>(a.dst[q], o + a.boff));
         }
 #pragma unroll
         for (int q = 0; q < 5; ++q) gst(a.dst[q], o, un[q]);
@@ -1070,8 +1079,8 @@ stage_kernel(BatchArgs ba) {
           R bxn = ((PU ? bs[0] : gld(a.src[5], o)) - tau_y * (S.ez[pm1][e_n] - S.ez[pm1][ex_me])) + tau_z * (ey_new - ey_prev);
           R byn = ((PU ? bs[PU ? 1 : 0] : gld(a.src[6], o)) - tau_z * (ex_new - ex_prev)) + tau_x * (S.ez[pm1][e_e] - S.ez[pm1][ex_me]);
           if constexpr (MODE == MODE_COMBINE) {
-            bxn = a.w * bxn + a.w0 * (PU ? b0[0] : gld<R>(a.dst[5], o + a.boff));
-            byn = a.w * byn + a.w0 * (PU ? b0[PU ? 1 : 0] : gld<R>(a.dst[6], o + a.boff));
+            bxn = weigh(a.w, bxn, a.w0, PU ? b0[0] : gld<R>(a.dst[5], o + a.boff));
+            byn = weigh(a.w, byn, a.w0, PU ? b0[PU ? 1 : 0] : gld<R>(a.dst[6], o + a.boff));
           }
           gst(a.dst[5], o, bxn);
           gst(a.dst[6], o, byn);
@@ -1101,7 +1110,7 @@ stage_kernel(BatchArgs ba) {
         } else if constexpr (CT == CT_FACE) {
           const int e_e = T::e(ci + 1, cj), e_n = T::e(ci, cj + 1);
           R bzn = (bz_m - tau_x * (S.ey[pm][e_e] - ey_new)) + tau_y * (S.ex[pm][e_n] - ex_new);
-          if constexpr (MODE == MODE_COMBINE) bzn = a.w * bzn + a.w0 * (PU ? b0[PU ? 2 : 0] : gld<R>(a.dst[7], o + a.boff));
+          if constexpr (MODE == MODE_COMBINE) bzn = weigh(a.w, bzn, a.w0, PU ? b0[PU ? 2 : 0] : gld<R>(a.dst[7], o + a.boff));
           gst(a.dst[7], o, bzn);
         } else {
           // vector-potential form: leave this column's three corner EMFs of
