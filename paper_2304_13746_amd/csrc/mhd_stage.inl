@@ -496,7 +496,7 @@ stage_kernel(BatchArgs ba) {
   auto& S = SA.s;
   constexpr bool EL = sizeof(R) == 8 && NB == 2;  // own EMFs of the plane before kept in LDS only
   constexpr bool CL = Carry<R, TX, TY>::in_lds && !MS;
-  constexpr bool PF = sizeof(R) == 4 && RECON != RECON_PPM;  // next-plane prefetch (below)
+  constexpr bool PF = sizeof(R) == 4 ? !PPM : PPM && !HY;  // next-plane prefetch (below)
 
   // XCD-aware order: the hardware deals blocks round-robin over 8 XCDs; give
   // each XCD a contiguous run of spatially adjacent tiles so halos hit its L2.
@@ -653,10 +653,13 @@ stage_kernel(BatchArgs ba) {
     const int km = wrapi(m, a.nz);
     // corner-EMF buffers of planes m and m-1
     const int pm = NB == 2 ? (m & 1) : 0, pm1 = NB == 2 ? (pm ^ 1) : 0;
-    // FP32: the next plane's state (and halo item) is loaded before the face
+    // FP32, and FP64 PPM with a field (one wave per SIMD, so it has the whole register
+    // file): the next plane's state (and halo item) is loaded before the face
     // solves, so its memory latency overlaps them (src is never written by this
-    // launch); FP64 and FP32 PPM have no registers to spare for all of it
-    // (measured: the spills cost more than the latency)
+    // launch); the other FP64 builds and FP32 PPM have no registers to spare for all
+    // of it (measured: the spills cost more than the latency).  FP64 PPM at 256^3, an RK3
+    // cycle: 20.4 ms with neither early load, 19.6 with this one, 18.3 with the one ahead
+    // of the corner EMFs, 17.5 with both (446 of 512 VGPRs)
     Raw<R> rnext, rxnext;
     // FP64 (PLM, LimO3): the own column's five conserved values of the next
     // plane ahead of the face solves (10 VGPRs; measured 1.9 % faster at 256^3.
@@ -981,10 +984,11 @@ stage_kernel(BatchArgs ba) {
     // comes first: after C without corner EMFs or with one EMF plane, after D
     // with them)
 
-    // FP32: what the update of plane m-1 reads from memory, ahead of the corner EMFs whose
-    // branches the compiler does not move loads across (256^3, a cycle 2.07 -> 2.00 ms; PPM
-    // has no registers for it: an RK3 cycle 9.0 ms with it, 8.7 without)
-    constexpr bool PU = sizeof(R) == 4 && !PPM && MODE != MODE_MEASURE;
+    // As for the next plane: what the update of plane m-1 reads from memory, ahead of the
+    // corner EMFs whose branches the compiler does not move loads across (FP32 at 256^3, a
+    // cycle 2.07 -> 2.00 ms; FP32 PPM has no registers for it: an RK3 cycle 9.0 ms with it,
+    // 8.7 without)
+    constexpr bool PU = (sizeof(R) == 4 ? !PPM : PPM && !HY) && MODE != MODE_MEASURE;
     constexpr bool FB = !NE && CT == CT_FACE;  // the face field is updated here
     const long long ou = (long long)wrapi(m - 1, a.nz) * plane + col;
     R u0[PU && MODE == MODE_COMBINE ? 5 : 1], bs[PU && FB ? 2 : 1], b0[PU && FB && MODE == MODE_COMBINE ? 3 : 1];
