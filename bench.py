@@ -438,8 +438,7 @@ def main():
     for prec in precs:
         r = run_gpu(state, prec, args.steps, args.warmup, args.tile, args.zchunk)
         ms_step = r["ms_total"] / args.steps
-        # two stage launches per cycle; the two one-thread cycle-control
-        # launches (a few microseconds) are charged to them, conservatively
+        # two stage launches per cycle, which also do the cycle control
         results[prec] = {"value": N ** 3 / (ms_step * 1e-3), "ms_per_step": ms_step,
                          "roofline": roofline(prec, ms_step / 2.0), "rc": r["rc"]}
         rf = results[prec]["roofline"]
