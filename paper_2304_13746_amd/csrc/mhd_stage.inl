@@ -48,6 +48,11 @@ struct StageArgs {
 };
 
 enum { MODE_STAGE1 = 0, MODE_COMBINE = 1, MODE_MEASURE = 2 };
+// Measuring eq. (cfl) takes the faces' signal speeds alone, no flux, EMF or update (a
+// 256^3 FP64 pass 2.57 -> 0.89 ms).  Not in FP32, where contraction rounds the speeds
+// differently without the fluxes beside them, and a first step has to be the same step.
+template <typename R, int MODE>
+constexpr bool kSpeedsOnly = MODE == MODE_MEASURE && sizeof(R) == 8;
 
 // State arrays live in global memory; loads and stores through these helpers
 // use global (not flat) instructions.
@@ -458,14 +463,14 @@ __device__ __forceinline__ void get_cell(const SM& S, int iw, Cell<R>& c) {
 // Measuring needs no fluxes and, but for FP64 PPM, fits one wave more again.
 template <typename R, bool HY, bool PPM, bool MS>
 struct Occupancy {
-  static constexpr int waves = sizeof(R) == 4 ? MHD_WAVES_F32 + (HY || MS ? 1 : 0)
+  static constexpr int waves = sizeof(R) == 4 ? MHD_WAVES_F32 + (HY ? 1 : 0)
                                : PPM          ? (HY ? MHD_WAVES_F64 : 1)
                                               : MHD_WAVES_F64 + (HY || MS ? 1 : 0);
 };
 
 template <typename R, int SOLVER, int RECON, int EMF, int CT, int MODE, int TX, int TY>
 __global__ void __launch_bounds__(TX * TY + 2 * (TX + TY))
-__attribute__((amdgpu_waves_per_eu(Occupancy<R, SOLVER == SOLVER_HLLC, RECON == RECON_PPM, MODE == MODE_MEASURE>::waves)))
+__attribute__((amdgpu_waves_per_eu(Occupancy<R, SOLVER == SOLVER_HLLC, RECON == RECON_PPM, kSpeedsOnly<R, MODE>>::waves)))
 stage_kernel(BatchArgs ba) {
   constexpr bool PPM = RECON == RECON_PPM;
   constexpr int H = PPM ? 3 : 2;
@@ -482,9 +487,7 @@ stage_kernel(BatchArgs ba) {
   // and solves only the faces the tile's own cells need (it leaves B alone)
   constexpr bool UCT = EMF == EMF_UCT || EMF == EMF_UCT_HLLD;
   constexpr int UK = UCT && MODE != MODE_MEASURE ? EMF : 0;  // which edge solve's face data to export
-  // measuring eq. (cfl) takes the faces' signal speeds alone: no flux, EMF or update
-  // (a 256^3 pass 2.57 -> 0.89 ms in FP64, 0.83 -> 0.43 in FP32)
-  constexpr bool MS = MODE == MODE_MEASURE;
+  constexpr bool MS = kSpeedsOnly<R, MODE>;
   constexpr bool NE = HY || UCT || MS;
   // FP64 PPM limits each cell's x and y faces once per plane into LDS (FP32 PPM
   // limits them per face: the extra 15 KB of LDS would cost it a block per CU,
@@ -1186,7 +1189,7 @@ static hipError_t launch_one(const BatchArgs& ba, hipStream_t st, bool prepare) 
   using T = Tile<TX, TY>;
   const size_t lds =
       sizeof(typename LdsLayout<R, TX, TY, SOLVER == SOLVER_HLLC, RECON == RECON_PPM ? 3 : 2,
-                                RECON == RECON_PPM && sizeof(R) == 8, MODE == MODE_MEASURE>::type);
+                                RECON == RECON_PPM && sizeof(R) == 8, kSpeedsOnly<R, MODE>>::type);
   auto fn = stage_kernel<R, SOLVER, RECON, EMF, CT, MODE, TX, TY>;
   if (prepare)
     return hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
