@@ -1,0 +1,85 @@
+"""Host code that plans launches, run against a HIP runtime without a GPU (fake_hip.c):
+what is launched, and what a call costs the host."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+COMMON = r"""
+import ctypes as C, sys, time
+sys.path.insert(0, sys.argv[2])
+fake = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+fake.fake_name.restype = C.c_char_p
+from paper_2304_13746_amd import _lib as L
+lib = L.lib()
+keep = []
+
+def box(nx, ny, nz, precision=L.MHD_FP32, tile=0, zchunk=0, **kw):
+    p = L.Params()
+    p.nx, p.ny, p.nz, p.precision, p.tile, p.zchunk = nx, ny, nz, precision, tile, zchunk
+    p.lx = p.ly = p.lz = 1.0
+    p.gamma, p.cfl = 5.0 / 3.0, 0.3
+    for k, v in kw.items():
+        setattr(p, k, v)
+    n = lib.mhd_workspace_bytes(C.byref(p))
+    buf = C.create_string_buffer(n + 256)
+    p.workspace, p.workspace_bytes = (C.addressof(buf) + 255) // 256 * 256, n
+    ctx = C.c_void_p()
+    assert lib.mhd_create(C.byref(p), C.byref(ctx)) == L.MHD_OK
+    keep.append(buf)
+    return ctx
+
+def shape(ctx):
+    t, z = C.c_int(), C.c_int()
+    assert lib.mhd_get_launch(ctx, C.byref(t), C.byref(z)) == L.MHD_OK
+    return t.value, z.value
+
+def launched():
+    out = [(fake.fake_name(i).decode(), fake.fake_grid(i)) for i in range(fake.fake_count())]
+    fake.fake_clear()
+    return out
+
+def step_batch(ctxs, n=1):
+    fake.fake_clear()
+    arr = (C.c_void_p * len(ctxs))(*[c.value for c in ctxs])
+    steps = (C.c_int * len(ctxs))(*([n] * len(ctxs)))
+    return lib.mhd_step_batch(arr, steps, len(ctxs), None)
+"""
+
+
+@pytest.fixture(scope="session")
+def fake_hip(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake_hip") / "libfake_hip.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-w", "-o", so, os.path.join(HERE, "fake_hip.c")],
+                   check=True)
+    return so
+
+
+def run(fake_hip, body):
+    """The body in a process of its own, whose libmhd.so binds to the fake runtime."""
+    r = subprocess.run([sys.executable, "-c", COMMON + body, fake_hip, os.path.dirname(HERE)],
+                       capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+    return r.stdout
+
+
+def test_one_box_is_planned_once(fake_hip):
+    """A step call of a box whose shape is automatic costs the host no search: about what
+    it costs with a shape that was asked for."""
+    run(fake_hip, r"""
+def cost(ctx):
+    best = 1.0
+    for _ in range(20):
+        t = time.perf_counter()
+        for _ in range(50):
+            lib.mhd_step(ctx, 1, 0.0)
+        best = min(best, time.perf_counter() - t)
+        fake.fake_clear()
+    return best
+auto, asked = box(16, 16, 4096), box(16, 16, 4096, tile=2, zchunk=32)
+a, b = cost(auto), cost(asked)
+assert a < 3.0 * b, (a, b)
+""")
