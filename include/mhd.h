@@ -218,6 +218,11 @@ int mhd_step_batch(mhd_ctx* const* ctxs, const int* nsteps, int n, void* stream)
  * mhd_get_launch still returns the columns' shape, and asking for it gives columns. */
 int mhd_set_launch(mhd_ctx* ctx, int tile, int zchunk);
 int mhd_get_launch(const mhd_ctx* ctx, int* tile, int* zchunk);
+/* What was asked for, by mhd_params, mhd_set_launch or mhd_tune: MHD_TILE_DEFAULT and 0
+ * where nothing was.  mhd_set_launch with these values launches another context of the
+ * same parameters as this one is launched (mhd_get_launch's would turn bricks into
+ * columns). */
+int mhd_get_launch_request(const mhd_ctx* ctx, int* tile, int* zchunk);
 
 typedef struct {
   int tile;          /* chosen tile (MHD_TILE_*) */

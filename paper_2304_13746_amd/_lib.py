@@ -30,7 +30,7 @@ TILE_16x16, TILE_24x8, TILE_18x11 = 1, 2, 3
 EXPORTED = ("mhd_workspace_bytes", "mhd_create", "mhd_set_state", "mhd_step", "mhd_get_state",
             "mhd_get_stage_output", "mhd_get_diagnostics", "mhd_get_diagnostics_noalloc",
             "mhd_step_batch", "mhd_set_launch",
-            "mhd_get_launch", "mhd_tune", "mhd_destroy", "mhd_status_string")
+            "mhd_get_launch", "mhd_get_launch_request", "mhd_tune", "mhd_destroy", "mhd_status_string")
 
 
 class Params(C.Structure):
@@ -90,6 +90,7 @@ def lib():
         L.mhd_step_batch.argtypes = [P(C.c_void_p), P(C.c_int), C.c_int, C.c_void_p]
         L.mhd_set_launch.argtypes = [C.c_void_p, C.c_int, C.c_int]
         L.mhd_get_launch.argtypes = [C.c_void_p, P(C.c_int), P(C.c_int)]
+        L.mhd_get_launch_request.argtypes = [C.c_void_p, P(C.c_int), P(C.c_int)]
         L.mhd_tune.argtypes = [P(C.c_void_p), C.c_int, C.c_int, C.c_void_p, P(TuneResult)]
         L.mhd_destroy.argtypes = [C.c_void_p]
         L.mhd_status_string.argtypes = [C.c_int]

@@ -73,7 +73,9 @@ class Tuner:
     def key(self, boxes) -> str:
         b0 = boxes[0]
         pr = b0.params
-        scheme = f"riemann{pr.riemann}/recon{pr.recon}/emf{pr.emf}"
+        # v2: entries that hold what was asked for; older ones hold the columns of a small
+        # group that was timed as bricks
+        scheme = f"riemann{pr.riemann}/recon{pr.recon}/emf{pr.emf}/v2"
         return group_key(self._device_name(b0), b0.precision, scheme,
                          [(b.shape[2], b.shape[1], b.shape[0]) for b in boxes])
 
@@ -82,8 +84,10 @@ class Tuner:
 
     def apply(self, boxes, choice: dict):
         per_nz = choice.get("zchunk_by_nz", {})
+        request = choice.get("request_by_nz", {})
         for b in boxes:
-            b.set_launch(choice["tile"], per_nz.get(str(b.shape[0]), choice["zchunk_cap"]))
+            nz = str(b.shape[0])
+            b.set_launch(*request.get(nz, (choice["tile"], per_nz.get(nz, choice["zchunk_cap"]))))
 
     def measure(self, boxes, stream=None) -> dict:
         """Time every candidate on the GPU (mhd_tune) and apply the fastest."""
@@ -93,11 +97,13 @@ class Tuner:
         st = stream if stream is not None else boxes[0].stream
         L.check(lib.mhd_tune(arr, len(boxes), self.reps, C.c_void_p(st.cuda_stream), C.byref(res)),
                 "mhd_tune")
-        # the z-planes per work-group each shape class ended with
+        # the z-planes per work-group each shape class ended with, and what it was asked for
+        # (an automatic shape stays one when the choice is applied again)
         per_nz = {str(b.shape[0]): b.get_launch()[1] for b in boxes}
+        request = {str(b.shape[0]): list(b.get_launch_request()) for b in boxes}
         return {"tile": res.tile, "zchunk_cap": res.zchunk_cap, "best_ms": res.best_ms,
                 "default_ms": res.default_ms, "candidates": res.candidates,
-                "zchunk_by_nz": per_nz}
+                "zchunk_by_nz": per_nz, "request_by_nz": request}
 
     def tune(self, boxes, stream=None, force: bool = False) -> dict:
         """Apply the cached shape for this group, or measure, store and apply."""

@@ -182,6 +182,13 @@ class MHDBox:
         L.check(self.lib.mhd_get_launch(self.ctx, C.byref(t), C.byref(z)), "mhd_get_launch")
         return t.value, z.value
 
+    def get_launch_request(self):
+        """The tile and z-planes per work-group asked for: (0, 0) where automatic."""
+        t, z = C.c_int(), C.c_int()
+        L.check(self.lib.mhd_get_launch_request(self.ctx, C.byref(t), C.byref(z)),
+                "mhd_get_launch_request")
+        return t.value, z.value
+
     def close(self):
         if self.ctx:
             self.lib.mhd_destroy(self.ctx)

@@ -1143,6 +1143,13 @@ int mhd_get_launch(const mhd_ctx* c, int* tile, int* zchunk) {
   return MHD_OK;
 }
 
+int mhd_get_launch_request(const mhd_ctx* c, int* tile, int* zchunk) {
+  if (!c) return MHD_ERR_INVALID_ARG;
+  if (tile) *tile = c->shaped ? c->tile : MHD_TILE_DEFAULT;
+  if (zchunk) *zchunk = c->zchunk;
+  return MHD_OK;
+}
+
 int mhd_tune(mhd_ctx* const* ctxs, int n, int reps, void* stream, mhd_tune_result* out) {
   Range range("mhd_tune");
   if (!ctxs || n < 1 || n > 4096 || reps < 1 || reps > 100) return MHD_ERR_INVALID_ARG;

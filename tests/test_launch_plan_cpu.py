@@ -83,3 +83,66 @@ auto, asked = box(16, 16, 4096), box(16, 16, 4096, tile=2, zchunk=32)
 a, b = cost(auto), cost(asked)
 assert a < 3.0 * b, (a, b)
 """)
+
+
+TUNE = r"""
+import os, tempfile, types
+from paper_2304_13746_amd.autotune import Tuner
+Tuner._device_name = staticmethod(lambda b: "fake")
+cache = os.path.join(tempfile.mkdtemp(), "tune.json")
+
+class Box:
+    '''What the tuner sees of an MHDBox.'''
+    def __init__(self, nx, ny, nz, precision):
+        self.lib, self.ctx = lib, box(nx, ny, nz, precision)
+        self.shape, self.precision = (nz, ny, nx), str(precision)
+        self.stream = types.SimpleNamespace(cuda_stream=0)
+        self.params = types.SimpleNamespace(riemann=0, recon=0, emf=0)
+    def set_launch(self, tile, zchunk):
+        assert lib.mhd_set_launch(self.ctx, tile, zchunk) == L.MHD_OK
+    def get_launch(self):
+        return shape(self.ctx)
+    def get_launch_request(self):
+        t, z = C.c_int(), C.c_int()
+        assert lib.mhd_get_launch_request(self.ctx, C.byref(t), C.byref(z)) == L.MHD_OK
+        return t.value, z.value
+
+TIME = C.CFUNCTYPE(C.c_float, C.c_char_p, C.c_uint)
+
+def boxes(dims, precision=L.MHD_FP32):
+    return [Box(*d, precision) for d in dims]
+
+def one_stage(group):
+    '''(kernel, blocks) of a first stage of the group'''
+    assert step_batch([b.ctx for b in group]) == L.MHD_OK
+    return launched()[0]
+
+def tuned(dims, time, precision=L.MHD_FP32):
+    '''A group tuned where a launch takes time(kernel, blocks), and one that takes the choice
+    from the cache.'''
+    f = TIME(lambda name, grid: time(name.decode(), grid))
+    fake.fake_time_of(f)
+    a, b = boxes(dims, precision), boxes(dims, precision)
+    choice = Tuner(cache).tune(a)
+    fake.fake_time_of(None)
+    assert not choice["cached"] and Tuner(cache).tune(b[::-1])["cached"]
+    assert choice["best_ms"] <= choice["default_ms"]
+    return a, b, choice
+"""
+
+
+def run_tune(fake_hip, body):
+    return run(fake_hip, TUNE + body)
+
+
+@pytest.mark.parametrize("dims", [[(16, 16, 16)], [(16, 16, 16), (24, 8, 8), (9, 30, 5)], [(32, 32, 32)]])
+def test_tuned_bricks_stay_bricks(fake_hip, dims):
+    """A small FP64 group that is fastest as bricks runs as bricks afterwards, also where the
+    choice comes from the cache."""
+    run_tune(fake_hip, f"dims = {dims}" + r"""
+a, b, choice = tuned(dims, lambda name, grid: 1.0 if "brick" in name else 2.0, L.MHD_FP64)
+plain = one_stage(boxes(dims, L.MHD_FP64))
+assert "brick" in plain[0]
+assert one_stage(a) == plain and one_stage(b) == plain
+assert all(x.get_launch_request() == (0, 0) for x in a + b)
+""")
