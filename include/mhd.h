@@ -238,10 +238,13 @@ typedef struct {
  * stream (NULL: the stream of ctxs[0]), and take the fastest common shape
  * (tile, min(cap, nz)); then refine per shape class: the contexts sharing nz,
  * class by class (most cells first), try every other cap with the rest fixed
- * and keep one that makes the group's launch more than 1 % faster.  Every
- * context is left in its chosen shape (mhd_get_launch reads it; for a group whose
- * best cap is automatic that is the length it was timed with; out->zchunk_cap
- * is the common cap, out->best_ms the final time).  The first-stage launch reads the current state
+ * and keep one that makes the group's launch more than 1 % faster.  Every context is
+ * left in the chosen shape: where that is automatic, a group of up to 64 contexts
+ * that runs as columns gets the tile and the length that it was timed with, while
+ * bricks, a larger group and a single context stay automatic
+ * (mhd_get_launch_request reads which).  out->tile is the chosen tile,
+ * out->zchunk_cap the common cap, out->best_ms the final time.
+ * The first-stage launch reads the current state
  * and writes only the second buffer and the CFL maximum of the cycle being
  * prepared, so the state, t and the next step are unchanged.  Contexts must
  * share device, precision, solver, integrator and tile (as mhd_step_batch).

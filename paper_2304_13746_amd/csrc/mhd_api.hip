@@ -1297,20 +1297,15 @@ int mhd_tune(mhd_ctx* const* ctxs, int n, int reps, void* stream, mhd_tune_resul
     rc = MHD_ERR_HIP;
   if (rc == MHD_OK)
     for (int i = 0; i < n && rc == MHD_OK; ++i) rc = apply_shape(ctxs[i], best_tile, cls_cap[i], !automatic(best_tile, cls_cap[i]));
-  // an automatic length depends on what is launched together: a group's is fixed as
-  // it was timed, so that mhd_get_launch reports it
-  if (rc == MHD_OK && n > 1) {
-    for (int i0 = 0; i0 < n; i0 += kMaxBatch) {
-      const int m = n - i0 < kMaxBatch ? n - i0 : kMaxBatch;
-      if (plan_brick(ctxs + i0, m) != BRICK_NONE) continue;  // nothing to fix
-      for (int i = 0; i < m && rc == MHD_OK; ++i)
-        rc = apply_shape(ctxs[i0 + i], best_tile, cls_cap[i0 + i], true);
-      short lz[kMaxBatch];
-      int tile;
-      plan_march(ctxs + i0, m, &tile, lz);
-      for (int i = 0; i < m && rc == MHD_OK; ++i)
-        if (cls_cap[i0 + i] == 0) rc = apply_shape(ctxs[i0 + i], best_tile, lz[i], true);
-    }
+  // What is automatic depends on what is launched together.  The columns of a group that
+  // goes out as one launch are fixed as they were timed, tile and length; bricks, which no
+  // request asks for, and the launches of a larger group, which may differ in their tile
+  // (and a batch has one), stay automatic.
+  if (rc == MHD_OK && n > 1 && n <= kMaxBatch) {
+    const Plan p = plan_launch(ctxs, n);
+    for (int i = 0; p.brick == BRICK_NONE && i < n && rc == MHD_OK; ++i)
+      rc = apply_shape(ctxs[i], p.tile, p.lz[i], true);
+    if (p.brick == BRICK_NONE) best_tile = p.tile;
   }
   free(cls_cap);
   if (e0) (void)hipEventDestroy(e0);

@@ -146,3 +146,33 @@ assert "brick" in plain[0]
 assert one_stage(a) == plain and one_stage(b) == plain
 assert all(x.get_launch_request() == (0, 0) for x in a + b)
 """)
+
+
+def test_tuned_group_runs_what_was_timed(fake_hip):
+    """Where the automatic launch wins with 18x11 columns, the group keeps that tile and that
+    length."""
+    run_tune(fake_hip, r"""
+dims = [(54, 55, 40), (54, 110, 80)]
+plain = one_stage(boxes(dims))
+assert "Li18ELi11E" in plain[0]
+a, b, choice = tuned(dims, lambda name, grid: 1.0 if (name, grid) == plain else 2.0)
+assert choice["tile"] == L.TILE_18x11 and choice["zchunk_cap"] == 0
+assert one_stage(a) == plain and one_stage(b) == plain
+assert {x.get_launch()[0] for x in a + b} == {L.TILE_18x11}
+""")
+
+
+def test_large_group(fake_hip):
+    """A group beyond one launch, whose launches may differ in what they take, steps after
+    tuning as it did before."""
+    run_tune(fake_hip, r"""
+dims = [(54, 55, 40)] * 64 + [(16, 16, 16)] * 3
+def all_stages(group):
+    assert step_batch([x.ctx for x in group]) == L.MHD_OK
+    return launched()
+for precision in (L.MHD_FP32, L.MHD_FP64):
+    plain = all_stages(boxes(dims, precision))
+    kinds = {k for k, _ in plain}
+    a, b, choice = tuned(dims, lambda name, grid: 1.0 if name in kinds else 2.0, precision)
+    assert all_stages(a) == plain
+""")
