@@ -228,7 +228,7 @@ typedef struct {
   int tile;          /* chosen tile (MHD_TILE_*) */
   int zchunk_cap;    /* chosen cap on z-planes per work-group (0 = automatic) */
   float best_ms;     /* median duration of one stage launch with that shape */
-  float default_ms;  /* the same for the default shape */
+  float default_ms;  /* the same for the automatic launch */
   int candidates;    /* shapes timed */
 } mhd_tune_result;
 
@@ -238,12 +238,14 @@ typedef struct {
  * stream (NULL: the stream of ctxs[0]), and take the fastest common shape
  * (tile, min(cap, nz)); then refine per shape class: the contexts sharing nz,
  * class by class (most cells first), try every other cap with the rest fixed
- * and keep one that makes the group's launch more than 1 % faster.  Every context is
+ * and keep one that makes the group's launch more than 1 % faster.  The automatic
+ * launch, the common shape and the refined one are then timed in turns, and a later
+ * one is kept if it is more than 1 % faster than those before it.  Every context is
  * left in the chosen shape: where that is automatic, a group of up to 64 contexts
  * that runs as columns gets the tile and the length that it was timed with, while
  * bricks, a larger group and a single context stay automatic
  * (mhd_get_launch_request reads which).  out->tile is the chosen tile,
- * out->zchunk_cap the common cap, out->best_ms the final time.
+ * out->zchunk_cap the common cap, out->best_ms the chosen launch's time in the turns.
  * The first-stage launch reads the current state
  * and writes only the second buffer and the CFL maximum of the cycle being
  * prepared, so the state, t and the next step are unchanged.  Contexts must

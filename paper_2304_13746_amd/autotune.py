@@ -2,7 +2,8 @@
 
 ``mhd_tune`` (libmhd) times the first-stage launch of a group of boxes, as one
 batched launch, for every stage-kernel tile and z-chunk cap, takes the fastest
-common shape and then refines the z-chunk per shape class (boxes sharing nz).
+common shape, refines the z-chunk per shape class (boxes sharing nz) and keeps
+what beats the automatic launch in turns with it.
 This module keys that choice by the GPU, the precision,
 the scheme (solver, reconstruction, EMF) and the multiset of box shapes, keeps
 it in a JSON file, and applies a cached choice on later calls without timing

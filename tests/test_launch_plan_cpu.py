@@ -162,6 +162,34 @@ assert {x.get_launch()[0] for x in a + b} == {L.TILE_18x11}
 """)
 
 
+def test_a_lucky_timing_is_not_kept(fake_hip):
+    """A shape that leads once and not again gives way to the automatic launch, as does a
+    shape class's; one that leads every time is kept."""
+    run_tune(fake_hip, r"""
+dims = [(64, 64, 64), (40, 64, 24)]
+plain = one_stage(boxes(dims))
+seen = {}
+def lucky(name, grid):
+    if (name, grid) == plain:
+        return 1.0
+    n = seen[name, grid] = seen.get((name, grid), 0) + 1
+    return 0.5 if n < 5 else 1.5  # the launches of the first timing
+a, b, choice = tuned(dims, lucky)
+assert one_stage(a) == plain and one_stage(b) == plain
+assert choice["zchunk_cap"] == 0 and choice["best_ms"] == choice["default_ms"] > 0.0
+
+one = boxes(dims)
+for x in one:
+    x.set_launch(L.TILE_16x16, 16)
+want = one_stage(one)
+os.remove(cache)
+a, b, choice = tuned(dims, lambda name, grid: 0.5 if (name, grid) == want else 1.0)
+assert one_stage(a) == want and one_stage(b) == want
+assert (choice["tile"], choice["zchunk_cap"]) == (L.TILE_16x16, 16)
+assert choice["best_ms"] < choice["default_ms"]
+""")
+
+
 def test_large_group(fake_hip):
     """A group beyond one launch, whose launches may differ in what they take, steps after
     tuning as it did before."""
