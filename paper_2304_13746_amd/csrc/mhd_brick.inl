@@ -191,7 +191,7 @@ brick_kernel(BatchArgs ba) {
     }
     const R bn = HY ? R(0) : S.bf[HY ? 0 : d][HY ? 0 : T::ri(i, j, k)];
     R g[7], cmax;
-    riemann<SOLVER, false>(a.gamma, a.igm1, as_prim(ql), as_prim(qr), bn, g, cmax);
+    riemann<SOLVER>(a.gamma, a.igm1, as_prim(ql), as_prim(qr), bn, g, cmax);
     S.cons[0][f] = g[0];
     S.cons[1 + d][f] = g[1];
     S.cons[1 + d1][f] = g[2];

@@ -37,7 +37,8 @@ struct Tol<float> {
 //   with a normal reciprocal.  Not for 0 or infinity, which give NaN: a density, a fan
 //   width or a star denominator that is zero has no meaningful flux either way.
 //   dsqrt: Goldschmidt's coupled steps for sqrt(x) and 1 / (2 sqrt(x)), then two steps
-//   with exact residuals; exact for 2^-968 <= x < 2^1022.  dsqrt0 takes zero too.
+//   with exact residuals; exact for 2^-968 <= x < 2^1022.  0 and infinity give
+//   NaN; dsqrt0 takes 0, but no negative number.
 // dvd stays IEEE: its numerators can be as small as a field's or a velocity's tail.
 // FP32 uses the hardware reciprocal and square root (about 1 ulp), whose error is far
 // below the FP32 state's own rounding over a run.
@@ -51,8 +52,7 @@ __device__ __forceinline__ double quotient(double a, double b, double y) {
   const double q = a * y;
   return __builtin_fma(__builtin_fma(-b, q, a), y, q);
 }
-__device__ __forceinline__ double dsqrt(double x) {
-  const double y = __builtin_amdgcn_rsq(x);
+__device__ __forceinline__ double sqrt_from(double x, double y) {  // y near 1 / sqrt(x)
   double g = x * y, h = 0.5 * y;
   const double r = __builtin_fma(-h, g, 0.5);
   h = __builtin_fma(h, r, h);
@@ -60,11 +60,11 @@ __device__ __forceinline__ double dsqrt(double x) {
   g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
   return __builtin_fma(__builtin_fma(-g, g, x), h, g);
 }
-__device__ __forceinline__ float dsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
+__device__ __forceinline__ double dsqrt(double x) { return sqrt_from(x, __builtin_amdgcn_rsq(x)); }
 __device__ __forceinline__ double dsqrt0(double x) {
-  const double g = dsqrt(x);
-  return x == 0.0 ? x : g;
+  return sqrt_from(x, __builtin_fmin(__builtin_amdgcn_rsq(x), 0x1p511));
 }
+__device__ __forceinline__ float dsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 __device__ __forceinline__ float dsqrt0(float x) { return __builtin_amdgcn_sqrtf(x); }
 __device__ __forceinline__ double rcp(double x) {
   const double y = recip_near(x);
@@ -273,10 +273,10 @@ __device__ __forceinline__ void recon_pair(R q0, R q1, R q2, R& lo, R& hi) {
   }
 }
 
-// Fast magnetosonic speed from a^2 = gamma p / rho, |B|^2 / rho and B_n^2 / rho.  ZERO: it
-// can be zero, with the negative face pressures that PPM can give (a limited face of PLM
-// or LimO3 lies between its cell and a neighbour).
-template <bool ZERO, typename R>
+// Fast magnetosonic speed from a^2 = gamma p / rho, |B|^2 / rho and B_n^2 / rho: 0 where
+// there is nothing to carry a wave (no field, and a pressure that is zero or, in a cell
+// that the status latches or at a face of PPM, negative).
+template <typename R>
 __device__ __forceinline__ R fast_speed(R gamma, R rho, R p, R bn, R b1, R b2) {
   R irho = rcp(rho);
   R a2 = (gamma * p) * irho;
@@ -285,20 +285,20 @@ __device__ __forceinline__ R fast_speed(R gamma, R rho, R p, R bn, R b1, R b2) {
   R cn2 = (bn * bn) * irho;
   R s = a2 + ca2;
   R disc = s * s - R(4) * (a2 * cn2);
-  // FP64: a root of a positive number; 2^-500 in place of 0 leaves s + root at s
-  const R least = sizeof(R) == 8 ? R(0x1p-1000) : R(0);
-  disc = disc > least ? disc : least;
-  const R c2 = R(0.5) * (s + dsqrt(disc));
-  return ZERO ? dsqrt0(c2) : dsqrt(c2);
+  if constexpr (sizeof(R) == 8)
+    disc = __builtin_fmax(disc, R(0));
+  else
+    disc = disc > R(0) ? disc : R(0);
+  return dsqrt0(R(0.5) * (s + dsqrt0(disc)));
 }
 
 // Sound speed of a face without a field: what fast_speed gives there, since the root of a
-// rounded square is exact (0 where the pressure is negative).
-template <bool ZERO, typename R>
+// rounded square is exact (0 where the pressure is not positive).
+template <typename R>
 __device__ __forceinline__ R sound_speed(R gamma, R rho, R p) {
   const R a2 = (gamma * p) * rcp(rho);
-  const R c2 = a2 < R(0) ? R(0) : a2;
-  return ZERO ? dsqrt0(c2) : dsqrt(c2);
+  const R c = dsqrt(a2);
+  return a2 <= R(0) ? R(0) : c;
 }
 
 // A face-frame primitive state: (rho, v_n, v_t1, v_t2, B_t1, B_t2, p).
@@ -352,13 +352,13 @@ __device__ __forceinline__ void thermo(const Prim<R>& w, R bn, R igm1, R& e, R& 
 
 // Outer signal speeds S_L = min(v_n) - max(c_f), S_R = max(v_n) + max(c_f) and the
 // face's largest |speed| for the CFL condition.
-template <bool ZERO, bool HYDRO = false, typename R>
+template <bool HYDRO = false, typename R>
 __device__ __forceinline__ void outer_speeds(R gamma, const Prim<R>& l, const Prim<R>& r, R bn,
                                              R& sl, R& sr, R& cmax) {
-  R cfl = HYDRO ? sound_speed<ZERO>(gamma, l.rho, l.p)
-                : fast_speed<ZERO>(gamma, l.rho, l.p, bn, l.b1, l.b2);
-  R cfr = HYDRO ? sound_speed<ZERO>(gamma, r.rho, r.p)
-                : fast_speed<ZERO>(gamma, r.rho, r.p, bn, r.b1, r.b2);
+  R cfl = HYDRO ? sound_speed(gamma, l.rho, l.p)
+                : fast_speed(gamma, l.rho, l.p, bn, l.b1, l.b2);
+  R cfr = HYDRO ? sound_speed(gamma, r.rho, r.p)
+                : fast_speed(gamma, r.rho, r.p, bn, r.b1, r.b2);
   R cfm = cfl > cfr ? cfl : cfr;
   R umin = l.un < r.un ? l.un : r.un;
   R umax = l.un > r.un ? l.un : r.un;
@@ -369,14 +369,14 @@ __device__ __forceinline__ void outer_speeds(R gamma, const Prim<R>& l, const Pr
 }
 
 // HLL flux (one averaged state between S_L and S_R).
-template <bool ZERO, typename R>
+template <typename R>
 __device__ __forceinline__ void flux_hll(R gamma, R igm1, const Prim<R>& l, const Prim<R>& r, R bn,
                                          R* f, R& cmax) {
   Cons<R> cl, cr;
   physical(l, bn, igm1, cl);
   physical(r, bn, igm1, cr);
   R sl, sr;
-  outer_speeds<ZERO>(gamma, l, r, bn, sl, sr, cmax);
+  outer_speeds(gamma, l, r, bn, sl, sr, cmax);
   if (sl >= R(0)) {
 #pragma unroll
     for (int q = 0; q < 7; ++q) f[q] = cl.f[q];
@@ -483,11 +483,11 @@ __device__ __forceinline__ void alfven_speeds(R sm, R abn, R sql, R sqr, R& ssl,
 // is built from (left for S*_L >= 0 or S_M >= 0 > S*_L, right otherwise) gets
 // its conserved vector and physical flux evaluated, with the same expressions
 // F*_a = F_a + S_a (U*_a - U_a) and F**_a = F*_a + S*_a (U**_a - U*_a).
-template <bool ZERO, typename R>
+template <typename R>
 __device__ __forceinline__ void flux_hlld(R gamma, R igm1, const Prim<R>& l, const Prim<R>& r, R bn,
                                           R* f, R& cmax) {
   R sl, sr;
-  outer_speeds<ZERO>(gamma, l, r, bn, sl, sr, cmax);
+  outer_speeds(gamma, l, r, bn, sl, sr, cmax);
   if (sl >= R(0) || sr <= R(0)) {  // supersonic: upwind physical flux
     Cons<R> c;
     physical(sl >= R(0) ? l : r, bn, igm1, c);
@@ -542,11 +542,11 @@ __device__ __forceinline__ void flux_hlld(R gamma, R igm1, const Prim<R>& l, con
 // part (zero B fluxes, no magnetic pressure, sound-speed bounds).  Contact speed
 // S* = (p_R - p_L + d_L u_L - d_R u_R) / (d_L - d_R), d_K = rho_K (S_K - u_K);
 // star state d_K/(S_K - S*) (1, S*, v1, v2, E/rho + (S* - u)(S* + p/d_K)).
-template <bool ZERO, typename R>
+template <typename R>
 __device__ __forceinline__ void flux_hllc(R gamma, R igm1, Prim<R> l, Prim<R> r, R* f, R& cmax) {
   l.b1 = l.b2 = r.b1 = r.b2 = R(0);
   R sl, sr;
-  outer_speeds<ZERO, true>(gamma, l, r, R(0), sl, sr, cmax);
+  outer_speeds<true>(gamma, l, r, R(0), sl, sr, cmax);
   if (sl >= R(0) || sr <= R(0)) {  // supersonic: upwind physical flux
     Cons<R> c;
     physical(sl >= R(0) ? l : r, R(0), igm1, c);
@@ -590,11 +590,11 @@ __device__ __forceinline__ void flux_hllc(R gamma, R igm1, Prim<R> l, Prim<R> r,
 //   **R: aL = S*_R sqL sqR / ((sqL + sqR) |B_n|), aR = 1 - aL,
 //        dL = S*_R betaL - aL u_L,
 //        dR = aR u_R - (u_R + S_R (chi_R - 1) + S*_R (betaR - chi_R)).
-template <bool ZERO, typename R>
+template <typename R>
 __device__ __forceinline__ void hlld_uct_coef(R gamma, const Prim<R>& l, const Prim<R>& r, R bn,
                                               R& al, R& ar, R& dl_, R& dr_) {
   R sl, sr, cmax;
-  outer_speeds<ZERO>(gamma, l, r, bn, sl, sr, cmax);
+  outer_speeds(gamma, l, r, bn, sl, sr, cmax);
   dl_ = R(0);
   dr_ = R(0);
   if (sl >= R(0)) {
@@ -671,15 +671,15 @@ __device__ __forceinline__ void hlld_uct_coef(R gamma, const Prim<R>& l, const P
 
 enum { SOLVER_HLLD = 0, SOLVER_HLL = 1, SOLVER_HLLC = 2 };
 
-template <int SOLVER, bool ZERO, typename R>
+template <int SOLVER, typename R>
 __device__ __forceinline__ void riemann(R gamma, R igm1, const Prim<R>& l, const Prim<R>& r, R bn,
                                         R* f, R& cmax) {
   if constexpr (SOLVER == SOLVER_HLL)
-    flux_hll<ZERO>(gamma, igm1, l, r, bn, f, cmax);
+    flux_hll(gamma, igm1, l, r, bn, f, cmax);
   else if constexpr (SOLVER == SOLVER_HLLC)
-    flux_hllc<ZERO>(gamma, igm1, l, r, f, cmax);
+    flux_hllc(gamma, igm1, l, r, f, cmax);
   else
-    flux_hlld<ZERO>(gamma, igm1, l, r, bn, f, cmax);
+    flux_hlld(gamma, igm1, l, r, bn, f, cmax);
 }
 
 // Corner-EMF schemes of Sec. 2.4 (Gardiner & Stone 2005): E^c upwinds the

@@ -213,17 +213,17 @@ struct Face {
 };
 
 // UCT = 0: no edge-solve data; EMF_UCT (UCT-HLL) or EMF_UCT_HLLD
-template <int D, int SOLVER, int UCT, bool ZERO, bool SPEED, typename R>
+template <int D, int SOLVER, int UCT, bool SPEED, typename R>
 __device__ __forceinline__ void solve_face(const StageArgs<R>& a, const R* ql, const R* qr, R bn,
                                            Face<R>& out) {
   R f[7];
   const Prim<R> l = as_prim(ql), r = as_prim(qr);
   if constexpr (SPEED) {  // the signal speed only
     R sl, sr;
-    outer_speeds<ZERO, SOLVER == SOLVER_HLLC>(a.gamma, l, r, bn, sl, sr, out.cmax);
+    outer_speeds<SOLVER == SOLVER_HLLC>(a.gamma, l, r, bn, sl, sr, out.cmax);
     return;
   }
-  riemann<SOLVER, ZERO>(a.gamma, a.igm1, l, r, bn, f, out.cmax);
+  riemann<SOLVER>(a.gamma, a.igm1, l, r, bn, f, out.cmax);
   to_grid<D>(f, out.cons);
   out.fb1 = f[5];
   out.fb2 = f[6];
@@ -231,7 +231,7 @@ __device__ __forceinline__ void solve_face(const StageArgs<R>& a, const R* ql, c
     // alpha+ = max(0, S_R), alpha- = max(0, -S_L) of the outer bounds and the
     // transverse velocities averaged with the HLL weights
     R sl, sr, cm;
-    outer_speeds<ZERO>(a.gamma, l, r, bn, sl, sr, cm);
+    outer_speeds(a.gamma, l, r, bn, sl, sr, cm);
     const R ap = sr > R(0) ? sr : R(0);
     const R am = sl < R(0) ? -sl : R(0);
     out.ap = ap;
@@ -240,7 +240,7 @@ __device__ __forceinline__ void solve_face(const StageArgs<R>& a, const R* ql, c
     out.vt2 = dvd(ap * l.v2 + am * r.v2, ap + am);
   } else if constexpr (UCT == EMF_UCT_HLLD) {
     // the HLLD coefficients and the transverse velocities they weight
-    hlld_uct_coef<ZERO>(a.gamma, l, r, bn, out.ap, out.am, out.dl, out.dr);
+    hlld_uct_coef(a.gamma, l, r, bn, out.ap, out.am, out.dl, out.dr);
     out.vt1 = out.ap * l.v1 + out.am * r.v1;
     out.vt2 = out.ap * l.v2 + out.am * r.v2;
   }
@@ -783,7 +783,7 @@ stage_kernel(BatchArgs ba) {
           bn = gld(a.src[5], (long long)km * plane + col);
         }
       }
-      solve_face<0, SOLVER, UK, PPM, MS>(a, ql, qr, bn, fx);
+      solve_face<0, SOLVER, UK, MS>(a, ql, qr, bn, fx);
       // the previous plane's exports were consumed before the last barrier
       if constexpr (NE) {
 #pragma unroll
@@ -836,7 +836,7 @@ stage_kernel(BatchArgs ba) {
           bn = gld(a.src[6], (long long)km * plane + col);
         }
       }
-      solve_face<1, SOLVER, UK, PPM, MS>(a, ql, qr, bn, fy);
+      solve_face<1, SOLVER, UK, MS>(a, ql, qr, bn, fy);
       if constexpr (NE) {
 #pragma unroll
         for (int q = 0; q < 5; ++q)
@@ -939,7 +939,7 @@ stage_kernel(BatchArgs ba) {
           qa[v] = hi;  // becomes top of cell m
         }
       }
-      if (m >= z0) solve_face<2, SOLVER, UK, PPM, MS>(a, top7, bot, bz_m, fz);
+      if (m >= z0) solve_face<2, SOLVER, UK, MS>(a, top7, bot, bz_m, fz);
       if constexpr (UK != 0) {
         if (real && m >= z0 && m < z1) put_uct<2, UK>(a, (long long)km * plane + col, fz);
       }
