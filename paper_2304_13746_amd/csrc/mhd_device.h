@@ -117,8 +117,11 @@ template <typename R>
 __device__ __forceinline__ R limo3_phi(R th) {
   R p3;
   if constexpr (sizeof(R) == 8) {
-    th = th > R(-0x1p1000) ? th : R(-0x1p1000);  // phi = 0 from -2 on; -inf has no residual
-    p3 = quotient(R(2) + th, R(3), R(1.0 / 3.0));
+    // a third, correctly rounded: the exact one is a sixth of an ulp or more away from any
+    // midpoint, and the two parts of 1/3 are far closer to it than that.  An infinite ratio
+    // and NaN come out as of a division.
+    const R a = R(2) + th;
+    p3 = __builtin_fma(a, 0x1.5555555555555p-2, a * 0x1.5555555555555p-56);
   } else {
     p3 = dvd(R(2) + th, R(3));
   }
