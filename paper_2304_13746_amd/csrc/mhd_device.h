@@ -295,13 +295,16 @@ __device__ __forceinline__ R fast_speed(R gamma, R rho, R p, R bn, R b1, R b2) {
   return dsqrt0(R(0.5) * (s + dsqrt0(disc)));
 }
 
-// Sound speed of a face without a field: what fast_speed gives there, since the root of a
-// rounded square is exact (0 where the pressure is not positive).
-template <typename R>
-__device__ __forceinline__ R sound_speed(R gamma, R rho, R p) {
-  const R a2 = (gamma * p) * rcp(rho);
-  const R c = dsqrt(a2);
-  return a2 <= R(0) ? R(0) : c;
+// Sound speed of a face without a field in FP64: what fast_speed gives there, since the
+// root of a rounded square is exact (0 where the pressure is not positive).  FP32's is not
+// (v_sqrt_f32 misses 2 % of the squares by an ulp), and takes fast_speed.
+__device__ __forceinline__ double sound_speed(double gamma, double rho, double p) {
+  const double a2 = (gamma * p) * rcp(rho);
+  const double c = dsqrt(a2);
+  return a2 <= 0.0 ? 0.0 : c;
+}
+__device__ __forceinline__ float sound_speed(float gamma, float rho, float p) {
+  return fast_speed(gamma, rho, p, 0.0f, 0.0f, 0.0f);
 }
 
 // A face-frame primitive state: (rho, v_n, v_t1, v_t2, B_t1, B_t2, p).
