@@ -71,6 +71,9 @@ __device__ __forceinline__ double rcp(double x) {
   return __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
 }
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+// with 1/0 = inf, for the density of a cell
+__device__ __forceinline__ double rcp0(double x) { return __builtin_amdgcn_div_fixup(rcp(x), x, 1.0); }
+__device__ __forceinline__ float rcp0(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ double dvd(double a, double b) { return a / b; }
 __device__ __forceinline__ float dvd(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
 // Quotient of normal numbers (no tails in the numerator).

@@ -100,7 +100,7 @@ __device__ __forceinline__ void to_prim(R rho, R mx, R my, R mz, R en, R bxl, R 
   c.bx = R(0.5) * (bxl + bxr);
   c.by = R(0.5) * (byl + byr);
   c.bz = R(0.5) * (bzl + bzr);
-  R irho = rcp(rho);
+  R irho = rcp0(rho);
   c.vx = mx * irho;
   c.vy = my * irho;
   c.vz = mz * irho;

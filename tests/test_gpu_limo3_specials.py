@@ -21,7 +21,7 @@ def test_limo3(what, riemann, emf):
     s.update({f: 0.1 * rng.uniform(-1.0, 1.0, shape) for f in ("mx", "my", "mz")})
     s.update({f: np.zeros(shape) for f in ("bx", "by", "bz")})
     if what == "overflow":  # ratios of either sign beyond the largest number
-        s["mx"][5, 6] = 0.0
+        s["rho"][5, 6] = 1.0
         s["mx"][5, 6, 4:13] = [0.0, 1e-310, 0.3, 0.3, 0.3 + 1e-16, -0.2, -0.2 - 3e-17, 1e-312, 0.0]
     else:
         s["en" if "nan" in what else "rho"][5, 6, 7] = {"nan": np.nan, "minus_nan": -np.nan,

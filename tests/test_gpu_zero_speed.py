@@ -68,3 +68,27 @@ def test_first_step(recon, riemann):
     # a cycle measures the step of the state that it starts from
     o = O.copy_state(s)
     assert dt == O.step(oracle_params(DIMS, riemann=riemann, recon=recon), o, 0.0, 1e-3, 1, check=False)[1]
+
+
+@pytest.mark.parametrize("zchunk", [0, 3])
+@pytest.mark.parametrize("riemann,recon,emf", [c for c in SCHEMES if c[0] != "hllc"])
+def test_no_density(riemann, recon, emf, zchunk):
+    """A cell without density that has momentum: infinite velocities, as a division gives."""
+    need_gpu()
+    rng = np.random.default_rng(7)
+    shape = DIMS[::-1]
+    s = {"rho": 1.0 + 0.2 * rng.random(shape), "en": 1.0 + 0.1 * rng.random(shape)}
+    s.update({f: 0.1 * rng.uniform(-1.0, 1.0, shape) for f in ("mx", "my", "mz")})
+    s.update({f: np.zeros(shape) for f in ("bx", "by", "bz")})
+    s["rho"][5, 6, 7] = 0.0
+    box = gpu_box(DIMS, riemann=riemann, recon=recon, emf=emf, zchunk=zchunk)
+    box.set_state(s, 0.0, 1e-3)
+    box.step(1)
+    g, t, dt, _ = box.get_state_numpy(check=False)
+    box.close()
+    o = O.copy_state(s)
+    to, dto, _ = O.step(oracle_params(DIMS, riemann=riemann, recon=recon, emf=emf), o, 0.0, 1e-3, 1,
+                        check=False)
+    assert (t, dt) == (to, dto)
+    for f in FIELDS:
+        assert np.array_equal(g[f], o[f], equal_nan=True), f
