@@ -38,7 +38,7 @@ struct Tol<float> {
 //   width or a star denominator that is zero has no meaningful flux either way.
 //   dsqrt: Goldschmidt's coupled steps for sqrt(x) and 1 / (2 sqrt(x)), then two steps
 //   with exact residuals; exact for 2^-968 <= x < 2^1022.  0 and infinity give
-//   NaN; dsqrt0 takes 0, but no negative number.
+//   NaN; dsqrt0 takes them too, for one instruction.
 // dvd stays IEEE: its numerators can be as small as a field's or a velocity's tail.
 // FP32 uses the hardware reciprocal and square root (about 1 ulp), whose error is far
 // below the FP32 state's own rounding over a run.
@@ -52,7 +52,8 @@ __device__ __forceinline__ double quotient(double a, double b, double y) {
   const double q = a * y;
   return __builtin_fma(__builtin_fma(-b, q, a), y, q);
 }
-__device__ __forceinline__ double sqrt_from(double x, double y) {  // y near 1 / sqrt(x)
+__device__ __forceinline__ double dsqrt(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
   double g = x * y, h = 0.5 * y;
   const double r = __builtin_fma(-h, g, 0.5);
   h = __builtin_fma(h, r, h);
@@ -60,9 +61,8 @@ __device__ __forceinline__ double sqrt_from(double x, double y) {  // y near 1 /
   g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
   return __builtin_fma(__builtin_fma(-g, g, x), h, g);
 }
-__device__ __forceinline__ double dsqrt(double x) { return sqrt_from(x, __builtin_amdgcn_rsq(x)); }
 __device__ __forceinline__ double dsqrt0(double x) {
-  return sqrt_from(x, __builtin_fmin(__builtin_amdgcn_rsq(x), 0x1p511));
+  return __builtin_amdgcn_div_fixup(dsqrt(x), 1.0, x);  // 0 and inf as of x / 1
 }
 __device__ __forceinline__ float dsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 __device__ __forceinline__ float dsqrt0(float x) { return __builtin_amdgcn_sqrtf(x); }
@@ -303,8 +303,8 @@ __device__ __forceinline__ R fast_speed(R gamma, R rho, R p, R bn, R b1, R b2) {
 // (v_sqrt_f32 misses 2 % of the squares by an ulp), and takes fast_speed.
 __device__ __forceinline__ double sound_speed(double gamma, double rho, double p) {
   const double a2 = (gamma * p) * rcp(rho);
-  const double c = dsqrt(a2);
-  return a2 <= 0.0 ? 0.0 : c;
+  const double c = dsqrt0(a2);
+  return a2 < 0.0 ? 0.0 : c;
 }
 __device__ __forceinline__ float sound_speed(float gamma, float rho, float p) {
   return fast_speed(gamma, rho, p, 0.0f, 0.0f, 0.0f);

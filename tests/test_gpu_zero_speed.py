@@ -1,6 +1,7 @@
 """FP64 bit for bit with the oracle where nothing carries a wave: cells without a field
 whose pressure is zero or negative.  The status is latched there, and the state that comes
-back beside it is what the scheme gives for a signal speed of zero."""
+back beside it is what the scheme gives for a signal speed of zero; and so for a cell
+without density and for speeds beyond the largest number."""
 import numpy as np
 import pytest
 
@@ -88,6 +89,30 @@ def test_no_density(riemann, recon, emf, zchunk):
     box.close()
     o = O.copy_state(s)
     to, dto, _ = O.step(oracle_params(DIMS, riemann=riemann, recon=recon, emf=emf), o, 0.0, 1e-3, 1,
+                        check=False)
+    assert (t, dt) == (to, dto)
+    for f in FIELDS:
+        assert np.array_equal(g[f], o[f], equal_nan=True), f
+
+
+@pytest.mark.parametrize("riemann,recon,emf", [c for c in SCHEMES if c[0] != "hllc"])
+@pytest.mark.parametrize("pressure", [1e200, np.inf])
+def test_infinite_speed(pressure, riemann, recon, emf):
+    """A speed whose square overflows: infinite, so the next step is zero."""
+    need_gpu()
+    rng = np.random.default_rng(3)
+    shape = DIMS[::-1]
+    p = 0.6 + 0.1 * rng.random(shape)
+    p[5, 6, 7] = pressure
+    s = {f: np.zeros(shape) for f in FIELDS}
+    s["rho"], s["en"] = 1.0 + 0.2 * rng.random(shape), p / (5.0 / 3.0 - 1.0)
+    box = gpu_box(DIMS, riemann=riemann, recon=recon, emf=emf)
+    box.set_state(s, 0.0, 1e-3)
+    box.step(2)
+    g, t, dt, _ = box.get_state_numpy(check=False)
+    box.close()
+    o = O.copy_state(s)
+    to, dto, _ = O.step(oracle_params(DIMS, riemann=riemann, recon=recon, emf=emf), o, 0.0, 1e-3, 2,
                         check=False)
     assert (t, dt) == (to, dto)
     for f in FIELDS:
