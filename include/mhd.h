@@ -197,7 +197,9 @@ int mhd_get_diagnostics_noalloc(mhd_ctx* ctx, mhd_diag* out);
  * launch) and which also begins and ends the cycle (MHD_EULER: one cycle-control
  * launch more); each box keeps its own step size, time and status latch, and gives
  * the same bits as mhd_step on it alone.  All contexts must share device, precision, solver,
- * integrator, EMF scheme, reconstruction and tile shape (else MHD_ERR_UNSUPPORTED); a null entry or a
+ * integrator, EMF scheme, reconstruction and tile shape (else MHD_ERR_UNSUPPORTED), where
+ * the tile that a context takes alone when nothing is asked of it (mhd_get_launch) counts
+ * as the default: a group of both runs the default.  A null entry or a
  * negative count is MHD_ERR_INVALID_ARG.  The contexts' own streams are not
  * synchronised with: order them against the batch stream first.  Asynchronous,
  * allocation-free, capture-safe. */

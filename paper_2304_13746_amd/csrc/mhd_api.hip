@@ -33,6 +33,7 @@ struct mhd_ctx {
   int tile, zchunk;  // launch shape as requested (zchunk 0 = automatic)
   bool shaped;       // tile or zchunk was requested: that shape, whatever the size
   int lone_tile, lz; // tile and z-planes per work-group: as requested, or when stepped alone
+  int auto_tile;     // tile when stepped alone with nothing requested
   int diag_blocks;
   int stages_valid;  // intermediate buffers hold the last cycle's stage results
 };
@@ -621,18 +622,20 @@ constexpr double kTile1811 = 1.04;
 
 void plan_march(mhd_ctx* const* c, int n, int* tile, short* lz) {
   int zmax = 0;
-  bool shaped = false;
+  bool shaped = false, one = true;
   for (int i = 0; i < n; ++i) {
     lz[i] = (short)c[i]->lz;
     shaped = shaped || c[i]->shaped;
+    one = one && c[i]->tile == c[0]->tile;
     if (c[i]->zchunk == 0 && c[i]->p.nz > zmax) zmax = c[i]->p.nz;
   }
-  *tile = c[0]->tile;
+  const int first = one ? c[0]->tile : default_tile(c[0]->p.precision);  // see same_group
+  *tile = first;
   if (zmax == 0) return;
   double best = 0.0;
   int pick = 0;
   for (int second = 0; second < (shaped ? 1 : 2); ++second) {
-    const int tl = second ? (int)TILE_18x11 : c[0]->tile;
+    const int tl = second ? (int)TILE_18x11 : first;
     // every length for one box (planned when it takes its launch shape, see plan_launch);
     // for a group, planned as boxes leave it, every length up to 16 and then steps of an
     // eighth
@@ -905,17 +908,26 @@ int apply_shape(mhd_ctx* c, int tile, int zchunk, bool shaped) {
   return MHD_OK;
 }
 
+// A group runs one tile: the one that every context has, or the default where each has that
+// or the tile that it takes by itself (what mhd_get_launch gives for a box of which nothing
+// was asked can be asked for without shutting the box out of a group).
+int group_tile(const mhd_ctx* c) {
+  return c->tile == c->auto_tile ? default_tile(c->p.precision) : c->tile;
+}
+
 bool same_group(mhd_ctx* const* ctxs, int n) {
   const mhd_ctx* c0 = ctxs[0];
+  bool one = true, fits = true;
   for (int i = 1; i < n; ++i) {
     const mhd_ctx* c = ctxs[i];
     if (c->p.precision != c0->p.precision || c->p.riemann != c0->p.riemann ||
         c->p.integrator != c0->p.integrator || c->p.emf != c0->p.emf ||
-        c->p.recon != c0->p.recon || c->p.ct != c0->p.ct || c->tile != c0->tile ||
-        c->device != c0->device)
+        c->p.recon != c0->p.recon || c->p.ct != c0->p.ct || c->device != c0->device)
       return false;
+    one = one && c->tile == c0->tile;
+    fits = fits && group_tile(c) == group_tile(c0);
   }
-  return true;
+  return one || fits;
 }
 
 }  // namespace
@@ -1010,10 +1022,17 @@ int mhd_create(const mhd_params* p, mhd_ctx** out) {
   // a cell per thread, up to two blocks a CU
   const long long db = (c->ncell + kDiagThreads - 1) / kDiagThreads;
   c->diag_blocks = (int)(db < kDiagBlocks ? db : kDiagBlocks);
-  if (apply_shape(c, tile, p->zchunk, p->tile != 0 || p->zchunk != 0) != MHD_OK) {
+  const bool shaped = p->tile != 0 || p->zchunk != 0;
+  if (shaped) {  // what it would take, before anything is asked for
+    short lz;
+    c->tile = default_tile(p->precision);
+    plan_march(&c, 1, &c->auto_tile, &lz);
+  }
+  if (apply_shape(c, tile, p->zchunk, shaped) != MHD_OK) {
     free(c);
     return MHD_ERR_HIP;
   }
+  if (!shaped) c->auto_tile = c->lone_tile;
   hipLaunchKernelGGL(k_set, dim3(1), dim3(1), 0, c->stream, c->sc, 0.0, 0.0, p->cfl);
   if (hipGetLastError() != hipSuccess) {
     free(c);

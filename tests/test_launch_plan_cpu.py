@@ -204,3 +204,23 @@ for precision in (L.MHD_FP32, L.MHD_FP64):
     a, b, choice = tuned(dims, lambda name, grid: 1.0 if name in kinds else 2.0, precision)
     assert all_stages(a) == plain
 """)
+
+
+def test_shapes_that_boxes_take_alone_can_be_asked_for(fake_hip):
+    """Boxes given what mhd_get_launch said of each of them still step together, though some
+    take 18x11 alone; other mixtures of tiles are refused as before."""
+    run(fake_hip, r"""
+dims = [(54, 55, 40), (64, 64, 64), (24, 16, 40)]
+for precision in (L.MHD_FP32, L.MHD_FP64):
+    alone = [shape(box(*d, precision)) for d in dims]
+    assert {t for t, _ in alone} == {L.TILE_18x11, L.TILE_24x8}
+    asked = [box(*d, precision, tile=t, zchunk=z) for d, (t, z) in zip(dims, alone)]
+    assert [shape(c) for c in asked] == alone
+    assert step_batch(asked) == L.MHD_OK
+    assert all("Li24ELi8E" in k for k, _ in launched())
+    assert step_batch(asked[:1] + [box(*dims[1], precision)]) == L.MHD_OK
+    for t in (L.TILE_16x16, L.TILE_18x11):
+        assert step_batch([box(*dims[1], precision, tile=t), box(*dims[2], precision)]) == L.MHD_ERR_UNSUPPORTED
+    assert step_batch([box(*d, precision, tile=L.TILE_18x11) for d in dims]) == L.MHD_OK
+    assert all("Li18ELi11E" in k for k, _ in launched())
+""")
