@@ -224,3 +224,14 @@ for precision in (L.MHD_FP32, L.MHD_FP64):
     assert step_batch([box(*d, precision, tile=L.TILE_18x11) for d in dims]) == L.MHD_OK
     assert all("Li18ELi11E" in k for k, _ in launched())
 """)
+
+
+def test_group_in_another_tile_than_alone(fake_hip):
+    """The group of the FP32 test of bits over tiles: its boxes take 18x11 alone and 24x8
+    together."""
+    run(fake_hip, r"""
+small, large = box(54, 55, 40), box(128, 96, 64)
+assert shape(small)[0] == L.TILE_18x11
+assert step_batch([small, large]) == L.MHD_OK
+assert all("Li24ELi8E" in k for k, _ in launched())
+""")
