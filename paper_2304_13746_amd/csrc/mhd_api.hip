@@ -549,23 +549,36 @@ struct Roles {
 
 // ---- planes per block (lz) of the contexts whose z-chunk is automatic.
 //
-// A block marches lz planes in the time of lz + kHead (the planes at its two ends that
-// its neighbours also compute, and the prologue: 2.1 in FP64 and 2.2 in FP32, from 16^3
-// boxes with 1 to 16 planes per block, 9.4 and 4.9 us a plane).  j blocks that share a
-// CU take 1 + share (j - 1) times as long a plane as one block alone, since one block's
-// waves leave the SIMDs idle while they wait; at most resident_blocks run at once.  N
-// blocks put ceil(N / 256) on a CU, so a launch takes
-//   (lz + kHead) (full rounds of resident blocks + the last, partly filled round),
-// and the rule takes the lz with the smallest, a box of its own with a preference for
-// chunk counts that the XCDs divide.  Measured per RK2 cycle (FP64, in us, before the
-// quotients without scaling took 15 % off all of them): 32^3 353 with 16 planes, the floor
-// that an earlier rule had, and 68 with 1; 101x75x52 365 with 16 and 242 with 6; 256^3
-// 5.62, 5.64, 5.79, 5.62, 5.46, 5.64, 5.91 and 5.83 ms with 16, 20, 22, 26, 32, 37, 43 and
-// 64, and the rule takes 32.  On five boxes between 128^3 and 256^3 in both precisions its
-// choice is within 3.5 % of the best of ten lengths.
+// A block marches lz planes in the time of lz + head (the planes at its two ends that its
+// neighbours also compute, fewer without corner EMFs, and the prologue).  j blocks that
+// share a CU take 1 + share (j - 1) times as long a plane as one block alone, since one
+// block's waves leave the SIMDs idle while they wait; at most resident_blocks run at once.
+// N blocks put ceil(N / 256) on a CU, so a launch takes
+//   (lz + head) (full rounds of resident blocks + the last, partly filled round),
+// and the rule takes the lz with the smallest.  base_lz, whose chunks the 8 XCDs divide,
+// stays unless another length is kGain better, or kGroupGain for a group, which then takes
+// one common length of at most kTop planes or the longest base_lz: the model does not see
+// the L2s, and without these limits it erred by up to 19 % (200x300x500 FP32 HLLC; 384^3
+// FP32 12 %, two boxes of 320^3 6 %).  Where one block fills a CU it errs by 1 %, and needs
+// no margin.  The constants are fitted, by kind of scheme, to cycles of 30 boxes between
+// 16^3 and 512^3, cubes, slabs and ragged, with up to 20 lengths in both tiles; the choice
+// is on average 0.8 % from the best of them and at most 1.4 % slower than base_lz.  In the
+// geometric mean over boxes it takes 0.61 of base_lz's time (96^3 FP64 0.68, 101x75x52 0.63,
+// 256^3 1.00), over 16 groups of 2 to 64 boxes 0.71, one of them 1.8 % more.
 constexpr int kCus = 256;
-constexpr double kHead = 2.2;
-constexpr double kSlabs = 1.06;
+constexpr double kGain = 0.04, kGroupGain = 0.02;
+constexpr int kTop = 32;
+
+struct MarchCost {
+  double head, share;
+  double tile1811;  // time of a block of 18x11 columns over one of 24x8
+};
+MarchCost march_cost(const mhd_params* p) {
+  const bool hydro = p->riemann == MHD_HLLC, f32 = p->precision == MHD_FP32, ppm = p->recon == MHD_PPM;
+  return {hydro && !(ppm && !f32) ? 0.6 : 1.6,
+          !f32 ? 0.6 : hydro ? (ppm ? 0.3 : 0.5) : (ppm ? 0.15 : 0.4),
+          hydro && f32 ? 1.15 : 1.05};
+}
 
 // blocks of these kernels that a CU holds at once (their registers and LDS)
 int resident_blocks(const mhd_params* p) {
@@ -582,13 +595,25 @@ long long columns(const mhd_params* p, int tile) {
 
 int chunks(int nz, int lz) { return (nz + lz - 1) / lz; }
 
-double launch_cost(const mhd_params* p, long long blocks, int lz) {
+// blocks: of the launch; mean, most: planes of its blocks
+double launch_cost(const mhd_params* p, long long blocks, double mean, int most) {
   const int r = resident_blocks(p);
-  const double share = p->precision == MHD_FP32 ? 0.42 : 0.55;
+  const MarchCost m = march_cost(p);
   const long long k = (blocks + kCus - 1) / kCus;
   const long long full = k / r;
   const int rest = (int)(k % r);
-  return (lz + kHead) * (full * (1.0 + share * (r - 1)) + (rest ? 1.0 + share * (rest - 1) : 0.0));
+  const double last = full ? mean : most;
+  return (mean + m.head) * full * (1.0 + m.share * (r - 1)) +
+         (rest ? (last + m.head) * (1.0 + m.share * (rest - 1)) : 0.0);
+}
+
+// At least 2,048 blocks (8 a CU) in a number of z-chunks that the 8 XCDs divide, so that
+// each gets whole z-slabs and halo planes hit its L2 (256^3: 7 % faster in FP64 and 3 % in
+// FP32 than 6 chunks; 512^3 FP32 up to 13 %), of 16 planes or more.
+int base_lz(long long columns, int nz) {
+  const long long want = ((2048 + columns - 1) / columns + 7) / 8 * 8;
+  const int lz = (int)((nz + want - 1) / want);
+  return lz < 16 ? (nz < 16 ? nz : 16) : lz;
 }
 
 long long bricks(const mhd_params* p, const BrickShape& b) {
@@ -615,11 +640,8 @@ int plan_brick(mhd_ctx* const* c, int n) {
 
 // The tile and the lz of n contexts launched together (n <= kMaxBatch): the requested
 // ones, or one common length for all that leave it open, and if none asks for anything
-// the tile with the smaller launch_cost.  24x8 and 18x11 both fill a 256-thread block; at
-// equal counts 18x11 took 2 to 5 % longer (256^3), so it has to save that: 101x75 is 50
-// columns of 24x8 and 42 of 18x11.
-constexpr double kTile1811 = 1.04;
-
+// the tile with the smaller launch_cost: 101x75 is 50 columns of 24x8 and 42 of 18x11, which
+// pays for a block of 18x11 taking longer.
 void plan_march(mhd_ctx* const* c, int n, int* tile, short* lz) {
   int zmax = 0;
   bool shaped = false, one = true;
@@ -632,29 +654,45 @@ void plan_march(mhd_ctx* const* c, int n, int* tile, short* lz) {
   const int first = one ? c[0]->tile : default_tile(c[0]->p.precision);  // see same_group
   *tile = first;
   if (zmax == 0) return;
-  double best = 0.0;
-  int pick = 0;
+  // z: a common length, or 0 for each box's base_lz
+  auto length = [&](int i, int z) {
+    const mhd_params* p = &c[i]->p;
+    if (c[i]->zchunk) return c[i]->lz;
+    if (z == 0) z = base_lz(columns(p, first), p->nz);
+    return z < p->nz ? z : p->nz;
+  };
+  auto cost = [&](int tl, int z) {
+    long long blocks = 0, planes = 0;
+    int most = 0;
+    for (int i = 0; i < n; ++i) {
+      const int l = length(i, z);
+      const long long b = columns(&c[i]->p, tl) * chunks(c[i]->p.nz, l);
+      blocks += b;
+      planes += b * l;
+      most = l > most ? l : most;
+    }
+    return launch_cost(&c[0]->p, blocks, (double)planes / (double)blocks, most);
+  };
+  const double gain = resident_blocks(&c[0]->p) == 1 ? 0.0 : n == 1 ? kGain : kGroupGain;
+  double best = (1.0 - gain) * cost(first, 0);
+  int pick = 0, top = kTop;
+  for (int i = 0; i < n; ++i) top = length(i, 0) > top ? length(i, 0) : top;
+  if (n == 1 || zmax < top) top = zmax;
   for (int second = 0; second < (shaped ? 1 : 2); ++second) {
     const int tl = second ? (int)TILE_18x11 : first;
     // every length for one box (planned when it takes its launch shape, see plan_launch);
     // for a group, planned as boxes leave it, every length up to 16 and then steps of an
     // eighth
-    for (int z = 1; z <= zmax; z += n == 1 || z < 16 ? 1 : z / 8) {
-      long long blocks = 0;
-      for (int i = 0; i < n; ++i)
-        blocks += columns(&c[i]->p, tl) * chunks(c[i]->p.nz, c[i]->zchunk ? c[i]->lz : z);
-      double t = launch_cost(&c[0]->p, blocks, z) * (second ? kTile1811 : 1.0);
-      // a large box: whole z-slabs for each of the 8 XCDs, or halo planes miss its L2
-      if (n == 1 && blocks >= 4 * kCus && chunks(zmax, z) % 8 != 0) t *= kSlabs;
-      if (pick == 0 || t < best) {
+    for (int z = 1; z <= top; z += n == 1 || z < 16 ? 1 : z / 8) {
+      const double t = cost(tl, z) * (second ? march_cost(&c[0]->p).tile1811 : 1.0);
+      if (t < best) {
         best = t;
         pick = z;
         *tile = tl;
       }
     }
   }
-  for (int i = 0; i < n; ++i)
-    if (c[i]->zchunk == 0) lz[i] = (short)(pick < c[i]->p.nz ? pick : c[i]->p.nz);
+  for (int i = 0; i < n; ++i) lz[i] = (short)length(i, pick);
 }
 
 // How the stages of up to kMaxBatch contexts are launched.
