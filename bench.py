@@ -32,13 +32,15 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-# Vector-ALU lane-operation rate: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 3.93e13
-# lane-ops/s, the same for FP64 and non-packed FP32 (packed FP32 is not used).
-LANE_OPS_PER_S = 256 * 4 * 16 * 2.4e9
+# Vector-ALU lane-operations per second: 64 lanes on each of 256 x 4 SIMDs at 2.4 GHz, a
+# wave instruction every 4 cycles in FP64 (measured 4.3 to 4.5 with two waves or more) and,
+# in FP32, every 2.5, the least measured (independent multiply-adds; compare and select
+# pairs take 3.1 to 3.5, selects and carries 4.3 to 4.5).  Packed FP32 is not used.
+LANE_OPS_PER_S = {"fp64": 64 * 1024 * 2.4e9 / 4.0, "fp32": 64 * 1024 * 2.4e9 / 2.5}
 # Flop ceilings of the two builds: FP64 is compiled without fused multiply-add
 # (every flop is one lane-op: 39.3 TFLOP/s); FP32 contracts multiply-adds (an
-# FMA is two flops: 78.6 TFLOP/s at most).
-ALU_PEAK_TFLOPS = {"fp64": LANE_OPS_PER_S / 1e12, "fp32": 2 * LANE_OPS_PER_S / 1e12}
+# FMA is two flops: 126 TFLOP/s at most).
+ALU_PEAK_TFLOPS = {"fp64": LANE_OPS_PER_S["fp64"] / 1e12, "fp32": 2 * LANE_OPS_PER_S["fp32"] / 1e12}
 # Algorithmic floating-point operations (add/sub, mul, div, sqrt) per cell and
 # stage of this method on this 256^3 input with HLLD, counted on the oracle by
 # oracle/opcount.cpp ("method_flops": every difference, slope, face state,
@@ -51,7 +53,7 @@ METRIC = "MHD cell-updates/s at 256^3 (FP64 vs FP32, %HBM peak); batched p50/p99
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("mhd_device.h", "mhd_stage.inl", "mhd_stage_launch.inl", "mhd_internal.h"):
+    for f in ("mhd_device.h", "mhd_stage.inl", "mhd_brick.inl", "mhd_stage_launch.inl", "mhd_internal.h"):
         with open(os.path.join(ROOT, "paper_2304_13746_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -165,7 +167,7 @@ def roofline(precision: str, launch_ms: float):
                               if precision == "fp64" else "FP32 with fused multiply-add"}}
     v = valu_per_cell(precision)
     if v is not None:
-        floor_ms = v * cells / LANE_OPS_PER_S * 1e3
+        floor_ms = v * cells / LANE_OPS_PER_S[precision] * 1e3
         out["valu"] = {"lane_instructions_per_cell_stage": round(v, 1),
                        "issue_floor_ms": round(floor_ms, 4),
                        "issue_frac": round(floor_ms / launch_ms, 4)}

@@ -1,7 +1,7 @@
 """Many uneven boxes advanced together: every stage launch of mhd_step_batch
 covers the tiles of all boxes, so small boxes fill the GPU together instead of
-one after another.  A box gives the same bits alone and in a batch: both go
-through the same kernel, tile by tile.
+one after another.  A box gives the same bits alone and in a batch, whatever tile
+each launch takes.
 
     boxes = [MHDBox(*dims, precision="fp32", stream=s) for dims in shapes]
     batch = BoxBatch(boxes)

@@ -92,10 +92,12 @@ __device__ __forceinline__ float dabs(float x) { return __builtin_fabsf(x); }
 // van Leer slope: harmonic mean of the one-sided differences if they share a
 // sign, zero otherwise.
 //
-// FP64 forms the quotient either way: as a branch around each of a plane's 35 limiters
-// it cut the face solves into blocks too small to schedule.  The product can be as small as a number gets (the square of a tail), so it is scaled by 2^104 on the way
-// into the quotient and the slope back on the way out, both exact: the residual's last
-// place is then above 2^-1074 for every product, and differences up to 2^459 pass.
+// FP64 forms the quotient either way: as a branch around each of a plane's 35 limiters it
+// cut the face solves into blocks too small to schedule.  The product can be as small as a
+// number gets (the square of a tail), so it is scaled by 2^104 on the way into the quotient
+// and the slope back on the way out: the residual's last place is then above 2^-1074 for
+// every product, and differences up to 2^459 pass.  Both scalings are exact, but for a slope
+// under 2^-1022, which is rounded twice.
 template <typename R>
 __device__ __forceinline__ R van_leer(R dm, R dp) {
   const R s = dp * dm;
