@@ -233,18 +233,17 @@ __device__ __forceinline__ bool uniform_line(const R (&q)[N][NV]) {
   return __all(e);
 }
 
-// The two states of a face, all variables.
-template <int RECON, bool HY, int NS, typename R>
+// The two states of a face, all variables, where the skip is built.  The other builds keep
+// their loop where it stands: called from here, FP32 PLM and LimO3 contract it differently.
+template <int RECON, int NS, typename R>
 __device__ __forceinline__ void line_states(const R (&q)[NS][7], R* ql, R* qr) {
-  if constexpr (kSkipUniform<R, RECON, HY> && RECON == RECON_LIMO3) {
-    if (__builtin_expect(uniform_line(q), 0)) {
+  if (__builtin_expect(uniform_line(q), 0)) {
 #pragma unroll
-      for (int v = 0; v < 7; ++v) {
-        ql[v] = q[1][v];
-        qr[v] = q[2][v];
-      }
-      return;
+    for (int v = 0; v < 7; ++v) {
+      ql[v] = q[1][v];
+      qr[v] = q[2][v];
     }
+    return;
   }
 #pragma unroll
   for (int v = 0; v < 7; ++v) face_states<RECON>(q, v, ql[v], qr[v]);
@@ -834,7 +833,12 @@ stage_kernel(BatchArgs ba) {
           get_cell<HY>(S, iw, c);
           frame_vals<0>(c, q[s]);
         }
-        line_states<RECON, HY>(q, ql, qr);
+        if constexpr (kSkipUniform<R, RECON, HY>) {
+          line_states<RECON>(q, ql, qr);
+        } else {
+#pragma unroll
+          for (int v = 0; v < 7; ++v) face_states<RECON>(q, v, ql[v], qr[v]);
+        }
       }
       R bn = R(0);
       if constexpr (!HY) {
@@ -886,7 +890,12 @@ stage_kernel(BatchArgs ba) {
           get_cell<HY>(S, iw, c);
           frame_vals<1>(c, q[s]);
         }
-        line_states<RECON, HY>(q, ql, qr);
+        if constexpr (kSkipUniform<R, RECON, HY>) {
+          line_states<RECON>(q, ql, qr);
+        } else {
+#pragma unroll
+          for (int v = 0; v < 7; ++v) face_states<RECON>(q, v, ql[v], qr[v]);
+        }
       }
       R bn = R(0);
       if constexpr (!HY) {
