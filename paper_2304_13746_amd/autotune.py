@@ -83,12 +83,16 @@ class Tuner:
     def lookup(self, boxes):
         return self._cache.get(self.key(boxes))
 
+    @staticmethod
+    def _dims(box) -> str:
+        return "x".join(str(n) for n in box.shape[::-1])
+
     def apply(self, boxes, choice: dict):
         per_nz = choice.get("zchunk_by_nz", {})
-        request = choice.get("request_by_nz", {})
+        request = choice.get("request_by_shape", {})
         for b in boxes:
             nz = str(b.shape[0])
-            b.set_launch(*request.get(nz, (choice["tile"], per_nz.get(nz, choice["zchunk_cap"]))))
+            b.set_launch(*request.get(self._dims(b), (choice["tile"], per_nz.get(nz, choice["zchunk_cap"]))))
 
     def measure(self, boxes, stream=None) -> dict:
         """Time every candidate on the GPU (mhd_tune) and apply the fastest."""
@@ -98,13 +102,13 @@ class Tuner:
         st = stream if stream is not None else boxes[0].stream
         L.check(lib.mhd_tune(arr, len(boxes), self.reps, C.c_void_p(st.cuda_stream), C.byref(res)),
                 "mhd_tune")
-        # the z-planes per work-group each shape class ended with, and what it was asked for
-        # (an automatic shape stays one when the choice is applied again)
+        # the z-planes per work-group each shape class ended with, and what each box was asked
+        # for (an automatic shape stays one when the choice is applied again)
         per_nz = {str(b.shape[0]): b.get_launch()[1] for b in boxes}
-        request = {str(b.shape[0]): list(b.get_launch_request()) for b in boxes}
+        request = {self._dims(b): list(b.get_launch_request()) for b in boxes}
         return {"tile": res.tile, "zchunk_cap": res.zchunk_cap, "best_ms": res.best_ms,
                 "default_ms": res.default_ms, "candidates": res.candidates,
-                "zchunk_by_nz": per_nz, "request_by_nz": request}
+                "zchunk_by_nz": per_nz, "request_by_shape": request}
 
     def tune(self, boxes, stream=None, force: bool = False) -> dict:
         """Apply the cached shape for this group, or measure, store and apply."""

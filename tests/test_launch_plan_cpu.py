@@ -163,6 +163,18 @@ assert {x.get_launch()[0] for x in a + b} == {L.TILE_18x11}
 """)
 
 
+def test_tuned_boxes_of_one_height(fake_hip):
+    """Boxes of one nz that keep lengths of their own, by what they cover, keep them through
+    the cache too."""
+    run_tune(fake_hip, r"""
+dims = [(320, 320, 192), (40, 32, 192)]
+plain = one_stage(boxes(dims))
+a, b, choice = tuned(dims, lambda name, grid: 1.0 if (name, grid) == plain else 2.0)
+assert len({x.get_launch()[1] for x in a}) == 2
+assert one_stage(a) == plain and one_stage(b) == plain
+""")
+
+
 def test_a_lucky_timing_is_not_kept(fake_hip):
     """A shape that leads once and not again gives way to the automatic launch, as does a
     shape class's; one that leads every time is kept."""
